@@ -17,7 +17,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include")]
-SOURCES = ["k_gemm.hip", "k_gemm_stream.hip", "k_attn.hip", "k_elem.hip", "k_moe.hip", "ods_api.cpp"]
+SOURCES = ["k_gemm.hip", "k_gemm_stream.hip", "k_gemm_skinny.hip", "k_attn.hip", "k_elem.hip", "k_moe.hip", "ods_api.cpp"]
 # The HIP-free host part (validation, allocator, sizing, planning) builds with
 # the host compiler alone; tests/test_host_sanitize.py builds it again under
 # the CPU sanitizers.

@@ -430,6 +430,7 @@ template <int EPI>
 hipError_t launch_epi(const GemmArgs &a, hipStream_t s) {
   const int bn = tile_n(a.N, a.K, EPI);
   const int n_tiles = (a.N + bn - 1) / bn;
+  if (!a.group_off && gemm_use_skinny(a.M, a.N, a.K, EPI, a.b_tiled != 0)) return launch_gemm_skinny(a, s);
   if (a.b_tiled) return launch_gemm_stream(a, s);  // tiled weights: K % 64 == 0 by contract
   if (a.a_gather && !(a.group_off && a.K % 64 == 0)) return hipErrorInvalidValue;  // only the streaming kernel gathers
   if (a.group_off) {

@@ -21,6 +21,8 @@ hipError_t launch_splitk_reduce(const GemmArgs &a, hipStream_t s);
 // Weight-streaming kernel (K % 64 == 0): dense GEMMs past 128 rows, of 33 to
 // 64 rows but the SiLU-gated one, grouped GEMMs, and every GEMM on tiled weights.
 hipError_t launch_gemm_stream(const GemmArgs &a, hipStream_t s);
+// Whole-K kernel for up to kSkinnyRows rows (dense GEMMs, both weight layouts, splits = 1).
+hipError_t launch_gemm_skinny(const GemmArgs &a, hipStream_t s);
 
 hipError_t launch_rmsnorm(const uint16_t *x, const uint16_t *gain, uint16_t *out, int rows, int H,
                           float eps, hipStream_t s);

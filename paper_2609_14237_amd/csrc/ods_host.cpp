@@ -134,6 +134,27 @@ int tile_n(int N, int K, int epi) {
   return (epi == EPI_SILU ? 2 * N : N) <= 8192 ? 32 : (epi == EPI_SILU ? 32 : 64);
 }
 
+// The whole-K kernel for up to 32 rows, except
+//  - wide outputs on tiled weights (a SiLU-gated N past 4096, a plain N past
+//    8192): the streaming kernel's blocks already read such a weight as long
+//    runs, without split-K (gate_up + SiLU of the 8B-shaped layer at 13 rows
+//    37.1 us there, 37.7 us here; row-major weights 47.7 -> 36.7 us);
+//  - from 17 rows, where a block reads twice the activation rows, narrow
+//    outputs (the router: its split-K sums fuse into top-k, 14.8 us both ways)
+//    and, past 32M elements, tiled weights and long K (down: tiled 25.7 us both
+//    ways at 24 rows, 25.9 there and 27.9 here at 32; row-major 27.3 there and
+//    29.4 here at 32). Smaller ones gain the partials and the reduce (o_proj at
+//    24 rows 14.0 -> 9.5 us), wide row-major ones the whole-line loads (gate_up
+//    + SiLU at 32 rows 48.0 -> 40.5 us).
+bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled) {
+  if (M > kSkinnyRows) return false;
+  if (b_tiled && N > (epi == EPI_SILU ? 4096 : 8192)) return false;
+  if (M <= 16) return true;
+  if (N <= 128) return false;
+  const bool large = (int64_t)N * K * (epi == EPI_SILU ? 2 : 1) > (int64_t)32 << 20;
+  return !large || (!b_tiled && !long_k(N, K, epi));
+}
+
 // Dense GEMMs past 128 rows, and those of 33 to 64 rows except the SiLU-gated
 // one (64-row tiles: at 64 rows qkv 20.2 -> 18.0 us, o_proj 16.4 -> 15.9 us and
 // down 31.8 -> 29.2 us on the 8B-shaped layer, gate_up level at 53 us and
@@ -188,6 +209,7 @@ int gemm_stream_splits(int M, int N, int K, int epi) {
 }
 
 int gemm_splits(int M, int N, int K, int epi, bool b_tiled) {
+  if (gemm_use_skinny(M, N, K, epi, b_tiled)) return 1;  // K is split over the waves of a block
   if (b_tiled || gemm_use_stream(M, N, K, epi)) return gemm_stream_splits(M, N, K, epi);
   if (N % 4 != 0) return 1;  // the reduce works on 4-column groups
   if (use_big(M, N)) {

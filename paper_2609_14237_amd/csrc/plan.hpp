@@ -49,6 +49,11 @@ struct GemmArgs {
 
 constexpr int kDecodeBM = 64, kDecodeBK = 128;  // decode-tile GEMM block rows and K step
 
+// Whole-K kernel for the smallest batches (k_gemm_skinny.hip): most rows it
+// takes, and the dense GEMMs that go to it.
+constexpr int kSkinnyRows = 32;
+bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled);
+
 // Decode-tile GEMM shape choices (row-major weights).
 bool use_big(int M, int N);            // 64 < M: the large-M tile
 bool long_k(int N, int K, int epi);    // narrow output with K >= 2N (the down projection)
