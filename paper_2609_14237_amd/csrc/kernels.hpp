@@ -27,6 +27,10 @@ hipError_t launch_gemm_skinny(const GemmArgs &a, hipStream_t s);
 hipError_t launch_rmsnorm(const uint16_t *x, const uint16_t *gain, uint16_t *out, int rows, int H,
                           float eps, hipStream_t s);
 
+// resid += sum of the split-K partials [splits][M][N], then out = RMSNorm(resid) * gain.
+hipError_t launch_reduce_norm(const float *partial, int splits, int M, int N, uint16_t *resid, const uint16_t *gain,
+                              float eps, uint16_t *out, hipStream_t s);
+
 // In-place RoPE of the q and k heads of qkv and/or append of k, v to the KV pool.
 // With splits > 1, each qkv row is first summed from the `splits` fp32 split-K
 // partials [splits][B][qkv width] (the same order and bf16 rounding as the

@@ -29,6 +29,12 @@ hipError_t execute(const Launch &L, hipStream_t s) {
   switch (L.kind) {
     case LK_RMSNORM: return launch_rmsnorm(L.x, L.gain, L.out, L.rows, L.width, L.eps, s);
     case LK_GEMM: return launch_gemm(L.gemm, s);
+    case LK_GEMM_NORM: {
+      const hipError_t e = launch_gemm(L.gemm, s);
+      if (e != hipSuccess) return e;
+      return launch_reduce_norm(L.gemm.partial, L.gemm.splits, L.gemm.M, L.gemm.N, (uint16_t *)L.gemm.C, L.gain, L.eps,
+                                L.out, s);
+    }
     case LK_QKV_ROPE:
     case LK_ROPE_APPEND: {
       if (L.kind == LK_QKV_ROPE) {

@@ -49,6 +49,9 @@ struct GemmArgs {
 
 constexpr int kDecodeBM = 64, kDecodeBK = 128;  // decode-tile GEMM block rows and K step
 
+// Widest row the fused split-K sum + RMSNorm holds in LDS (32 KB as bf16).
+constexpr int kReduceNormMaxN = 16384;
+
 // Whole-K kernel for the smallest batches (k_gemm_skinny.hip): most rows it
 // takes, and the dense GEMMs that go to it.
 constexpr int kSkinnyRows = 32;
@@ -121,7 +124,7 @@ ods_status validate_range(const ods_block *blk, int op_begin, int op_end, const 
 
 // One launch of a validated range.
 enum LaunchKind {
-  LK_RMSNORM, LK_GEMM, LK_QKV_ROPE, LK_ROPE_APPEND, LK_ATTENTION, LK_SILU, LK_TOPK, LK_ROUTER_TOPK, LK_PERMUTE,
+  LK_RMSNORM, LK_GEMM, LK_GEMM_NORM, LK_QKV_ROPE, LK_ROPE_APPEND, LK_ATTENTION, LK_SILU, LK_TOPK, LK_ROUTER_TOPK, LK_PERMUTE,
   LK_COMBINE
 };
 struct RopeArgs {
@@ -142,10 +145,10 @@ struct Launch {
   int layer;
   int n_ops;         // operators this launch covers (more than one when fused)
   const char *what;  // static name for traces and errors
-  GemmArgs gemm;     // LK_GEMM, LK_QKV_ROPE, LK_ROUTER_TOPK
+  GemmArgs gemm;     // LK_GEMM, LK_GEMM_NORM, LK_QKV_ROPE, LK_ROUTER_TOPK
   RopeArgs rope;     // LK_QKV_ROPE, LK_ROPE_APPEND
   AttnArgs attn;     // LK_ATTENTION
-  // LK_RMSNORM: x -> out with gain; LK_SILU: x (gate | up) -> out; LK_COMBINE: x (yp) into out (resid)
+  // LK_RMSNORM: x -> out with gain; LK_GEMM_NORM: the GEMM's split-K sum into resid, then its norm -> out with gain; LK_SILU: x (gate | up) -> out; LK_COMBINE: x (yp) into out (resid)
   const uint16_t *x, *gain; uint16_t *out; int rows, width; float eps;
   // LK_TOPK, LK_ROUTER_TOPK, LK_PERMUTE, LK_COMBINE
   const float *logits; float *weights; int32_t *ids, *perm, *slot_pos, *expert_off; int E, k;
