@@ -6,7 +6,7 @@
 // Work split: the (sequence b, KV head g, page of b's attended window) units
 // of the whole batch are numbered b-major, and wave r of the grid takes the
 // contiguous unit range [r*S, (r+1)*S) with S = ceil(total / waves) (at least
-// 8 pages), so every wave streams the same number of KV bytes however ragged
+// attn_min_pages), so every wave streams the same number of KV bytes however ragged
 // the contexts are. A range may end inside a sequence or cover several short
 // ones; each (b, g) piece is a segment. A sequence that one segment covers is
 // written to o directly; otherwise every segment leaves a partial record
@@ -29,7 +29,7 @@
 // pages with direct-to-LDS loads into a ring of two page slots of its own and
 // reads a slot into registers once its loads have landed, so the page in
 // flight costs no registers. The group's q rows are read once per segment,
-// not once per page. The page ids of the next 64 pages load while the current
+// with the loads of its first page. The page ids of the next 64 pages load while the current
 // 64 are streamed.
 #include <math.h>
 
@@ -43,9 +43,15 @@ namespace ods {
 namespace {
 
 constexpr int kNonTemporal = 2;  // cache-policy operand of the direct-to-LDS load: nt
-// Largest dynamic LDS a launch asks for: the per-sequence arrays at the batch
-// limit plus two K+V page slots for each of the four waves at D = 128.
-constexpr size_t kMaxAttnLds = ((2 * (size_t)kMaxAttnBatch + 1) * sizeof(int) + 15) / 16 * 16 + 4 * 2 * 2 * 16 * 128 * 2;
+constexpr int kSlots = 2;  // page slots per wave
+// Rows up to which four waves merge each (two blocks per compute unit).
+constexpr int64_t kMergeFewRows = 512;
+// Bytes of one slot: K block, V block, and the 16 query rows of a segment that
+// starts with the page.
+constexpr int attn_slot_bytes(int D) { return 2 * kPage * D * 2 + 16 * D * 2; }
+constexpr size_t attn_lds_bytes(int B, int D) {  // per-sequence arrays, then every wave's slots
+  return ((2 * (size_t)B + 1) * sizeof(int) + 15) / 16 * 16 + (size_t)attn_waves(D) * kSlots * attn_slot_bytes(D);
+}
 
 template <int D>
 struct PageRegs {
@@ -78,7 +84,7 @@ __device__ __forceinline__ void window_of(int ctx, int window, int &p, int &lo, 
 }
 
 template <int D>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_flat_kernel(
+__global__ __launch_bounds__(64 * attn_waves(D)) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_flat_kernel(
     const uint16_t *__restrict__ qkv, int n_q, int n_kv, int window, const int32_t *__restrict__ ctx_lens,
     const int32_t *__restrict__ page_table, int max_pages, int ring, const uint16_t *__restrict__ pool,
     int64_t pool_pages, int seg_pages, float scale_log2, float *__restrict__ ws_acc, float *__restrict__ ws_ml,
@@ -89,7 +95,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   extern __shared__ int smem_i[];
   int *s_pre = smem_i;          // [B + 1]: first unit of sequence b (its KV head 0)
   int *s_ctx = smem_i + B + 1;  // [B]: context (clamped to the page table unless it is a ring)
-  __shared__ int s_wtot[4];
+  constexpr int WAVES = attn_waves(D), THREADS = 64 * WAVES;
+  __shared__ int s_wtot[WAVES];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: keeps control flow scalar
@@ -101,7 +108,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   // ---- per-sequence contexts and the unit prefix s_pre[b] = n_kv * sum_{b' < b} pages(b')
   {
-    const int per = (B + 255) / 256;
+    const int per = (B + THREADS - 1) / THREADS;
     const int b0 = min(B, tid * per), b1 = min(B, b0 + per);
     int loc = 0;
     for (int b = b0; b < b1; ++b) {
@@ -126,17 +133,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       s_pre[b] = run * n_kv;
       run += n;
     }
-    if (tid == 255) s_pre[B] = run * n_kv;
+    if (tid == THREADS - 1) s_pre[B] = run * n_kv;
     __syncthreads();
   }
   // This wave's LDS page slots, after the per-sequence arrays: K block, then V block.
-  constexpr int kSlots = 2;
-  constexpr int SLOT = 2 * kPage * D * 2;
+  constexpr int SLOT = attn_slot_bytes(D);
   constexpr int LPP = 2 * (kPage * D * 2 / 1024);  // 16-byte direct-to-LDS loads per page and lane
   uint8_t *const slots = (uint8_t *)smem_i + (((2 * B + 1) * 4 + 15) & ~15) + wave * kSlots * SLOT;
   const int total = __builtin_amdgcn_readfirstlane(s_pre[B]);
-  const int n_waves = gridDim.x * 4;
-  const int S = seg_pages > 0 ? seg_pages : max(8, (total + n_waves - 1) / n_waves);
+  const int n_waves = gridDim.x * WAVES;
+  const int S = seg_pages > 0 ? seg_pages : max(attn_min_pages(D), (total + n_waves - 1) / n_waves);
   const int64_t page_stride = 2 * (int64_t)n_kv * BLK;
   const int64_t v_off = (int64_t)n_kv * BLK;
 
@@ -150,7 +156,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     return b;
   };
 
-  for (int r = blockIdx.x * 4 + wave; (int64_t)r * S < total; r += n_waves) {
+  for (int r = blockIdx.x * WAVES + wave; (int64_t)r * S < total; r += n_waves) {
     const int u0 = r * S, n_w = min(total, u0 + S) - u0;  // this range: units [u0, u0 + n_w)
 
     // Page ids of range pages [t0, t0 + 64), one per lane (-1 past the range):
@@ -184,6 +190,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       ipage = off % in_b;
     }
     int it = 0;  // range page index of the next issue
+    int iq_seq = -1;  // segment whose query rows were issued last
     int ids_cur = gather_ids(0), ids_nxt = gather_ids(64);
 
     // Issue the loads of the cursor's page into LDS slot `slot`, describe it
@@ -204,6 +211,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       R.ok = live && (unsigned)page < (unsigned long long)pool_pages;
       const uint16_t *kb = pool + (int64_t)ig * BLK + (int64_t)(R.ok ? page : 0) * page_stride;
       uint8_t *const dst = slots + slot * SLOT;
+      // The first page of a segment brings the segment's query rows along, ahead
+      // of its K/V loads: lane l fetches q[head l % 16][kk * 32 + (l / 16) * 8 ..],
+      // the fragment it reads back. They are in flight with the pages, so a new
+      // segment costs no drain of the page stream; loads complete in order, so
+      // a wait that counts page loads only covers them too.
+      if (live && R.seq != iq_seq) {
+        iq_seq = R.seq;
+        const uint16_t *qp = qkv + (int64_t)ib * row_elems + (int64_t)(ig * group + (head_ok ? hl : 0)) * D;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+          __builtin_amdgcn_global_load_lds((const void *)(qp + kk * 32 + rq * 8),
+                                           (__attribute__((address_space(3))) void *)(dst + 2 * kPage * D * 2 + kk * 1024),
+                                           16, 0, 0);
+      }
       // A direct-to-LDS load writes lane l's 16 bytes at byte 16 l of its
       // destination. K: lane l fetches the 16 bytes it will read as its MFMA
       // fragment (K[t = l % 16][kk * 32 + (l / 16) * 8 ..]), so its read-back is
@@ -335,12 +356,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       }
     };
 
-    // Two pages in flight through the wave's LDS slots: while one is consumed
-    // the next is loading; the stream runs across segment boundaries without
-    // draining. A wave's loads complete in order, so slot s has landed once
-    // only the other slot's LPP loads are outstanding. The q rows of a segment
-    // are loaded when its first page is consumed, and that path alone waits
-    // for every load.
+    // kSlots pages in flight through the wave's LDS slots: while one is consumed
+    // the others are loading; the stream runs across segment boundaries without
+    // draining. A wave's loads complete in order, so slot s has landed once at
+    // most the LPP page loads of each other slot are outstanding. A segment's
+    // query rows move to registers with its first page.
     PageMeta ms[kSlots];
     u32x4 qreg[KK];
     int q_seq = -1;
@@ -360,13 +380,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             R.v[nb] = *(const u32x2 *)(src + kPage * D * 2 + (nb * 16 + hl) * 32 + rq * 8);
           if (ms[sl].seq >= 0 && ms[sl].seq != q_seq) {
             q_seq = ms[sl].seq;
-            const int qb = q_seq / n_kv, qg = q_seq % n_kv;
-            const uint16_t *qp = qkv + (int64_t)qb * row_elems + (int64_t)(qg * group + (head_ok ? hl : 0)) * D;
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) qreg[kk] = *(const u32x4 *)(qp + kk * 32 + rq * 8);
-            // vmcnt(0) on this path only (a builtin, so the compiler knows the q
-            // registers have landed and adds no wait on the common path)
-            __builtin_amdgcn_s_waitcnt(0x0F70);
+            for (int kk = 0; kk < KK; ++kk)
+              qreg[kk] = *(const u32x4 *)(src + 2 * kPage * D * 2 + kk * 1024 + lane * 16);
           }
 #pragma unroll
           for (int kk = 0; kk < KK; ++kk) R.q[kk] = qreg[kk];
@@ -387,23 +403,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-// One wave per (sequence, query head): a sequence split into several segments
-// gets o[d] = sum_c 2^(m_c - M) acc_c[d] / sum_c 2^(m_c - M) l_c over its
-// records; a row with no context gets zeros; single-segment rows were written
-// by the attention kernel.
-template <int D>
+// A (sequence, query head) row split into several segments gets
+// o[d] = sum_c 2^(m_c - M) acc_c[d] / sum_c 2^(m_c - M) l_c over its records; a
+// row with no context gets zeros; single-segment rows were written by the
+// attention kernel. WPR waves share a row (1 or 4), each as 64 / (D / 4) groups
+// of lanes, and the groups take every G-th record, 16 bytes a lane.
+// Bound by latency: the metadata, then the records, one dependent round trip
+// each if all of a group's records fit its first four loads. With one wave per
+// row and one record at a time the 24 records of one 3000-token sequence took
+// six trips: attention and merge 22.2 -> 16.8 us (13 ragged sequences 33.6 ->
+// 30.1 us). Four waves a row pay while rows are few and are wasted waves once
+// the rows alone fill the chip.
+template <int D, int WPR>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict__ ws_acc,
                                                          const float *__restrict__ ws_ml,
                                                          const int2 *__restrict__ ws_meta, int n_q, int n_kv,
                                                          const int32_t *__restrict__ ctx_lens,
                                                          uint16_t *__restrict__ o, int B) {
-  constexpr int DPL = D / 64;  // d values per lane
-  const int lane = threadIdx.x & 63;
-  const int64_t wid = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  constexpr int LPR = D / 4, RPW = kWave / LPR;  // lanes per record, records a wave reads at once
+  constexpr int G = WPR * RPW, kPre = 4;
+  __shared__ float part[WPR > 1 ? 4 * D : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t wid = (int64_t)blockIdx.x * (4 / WPR) + (WPR > 1 ? 0 : wave);
   if (wid >= (int64_t)B * n_q) return;
   const int b = (int)(wid / n_q), h = (int)(wid % n_q);
   const int group = n_q / n_kv;
-  uint16_t *dst = o + wid * D + lane * DPL;
+  const int d = (lane % LPR) * 4;
+  const int grp = (WPR > 1 ? wave * RPW : 0) + lane / LPR;
+  uint16_t *dst = o + wid * D + d;
+  const bool writer = lane < LPR && (WPR == 1 || wave == 0);
   // The context and the merge metadata load together (the metadata of an
   // empty sequence is never used).
   const int ctx = ctx_lens[b];
@@ -412,25 +440,18 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
   // otherwise sink it past the branch and wait for the context first).
   asm volatile("" ::"v"(meta.x), "v"(meta.y));
   if (ctx < 1) {
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) dst[i] = 0;
+    if (writer) *(u32x2 *)dst = u32x2{0u, 0u};
     return;
   }
   const int n_seg = meta.y;
   if (n_seg <= 1) return;  // written by the attention kernel
   const int64_t rec0 = (int64_t)meta.x * group + h % group;  // records rec0 + c * group
-  // The accumulators of the first kPre records load together with the (m, l)
-  // pairs (neither depends on the other), so a sequence split a few ways costs
-  // one round trip after the metadata instead of two.
-  constexpr int kPre = 4;
-  float pre[kPre][DPL];
+  auto acc_of = [&](int c) { return *(const f32x4 *)(ws_acc + (rec0 + (int64_t)c * group) * D + d); };
+  f32x4 pre[kPre];  // loaded together with the (m, l) pairs: neither depends on the other
 #pragma unroll
-  for (int c = 0; c < kPre; ++c) {
-    if (c < n_seg) {
-      const float *src = ws_acc + (rec0 + (int64_t)c * group) * D + lane * DPL;
-#pragma unroll
-      for (int i = 0; i < DPL; ++i) pre[c][i] = src[i];
-    }
+  for (int i = 0; i < kPre; ++i) {
+    const int c = grp + i * G;
+    pre[i] = c < n_seg ? acc_of(c) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
   // (m, l) of record c as one 8-byte load; lane c keeps record c (< 64).
   auto ml_of = [&](int c) { return *(const float2 *)(ws_ml + (rec0 + (int64_t)c * group) * 2); };
@@ -439,40 +460,42 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
   for (int c = lane + 64; c < n_seg; c += 64) mloc = fmaxf(mloc, ml_of(c).x);
   const float M = wave_max(mloc);
   auto weight_of = [&](float mc) { return mc == -INFINITY ? 0.f : exp2f(mc - M); };
-  float lsum = weight_of(own.x) * own.y;
+  const float wl = weight_of(own.x);
+  float lsum = wl * own.y;
   for (int c = lane + 64; c < n_seg; c += 64) {
     const float2 r = ml_of(c);
     lsum += weight_of(r.x) * r.y;
   }
   const float L = wave_sum(lsum);
-  float acc[DPL];
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < DPL; ++i) acc[i] = 0.f;
-  if (n_seg <= kPre) {
-    const float wl = lane < n_seg ? weight_of(own.x) : 0.f;
-#pragma unroll
-    for (int c = 0; c < kPre; ++c) {
-      if (c < n_seg) {
-        const float w = __shfl(wl, c, kWave);
-#pragma unroll
-        for (int i = 0; i < DPL; ++i) acc[i] += w * pre[c][i];
-      }
-    }
+  for (int i = 0; i < kPre; ++i) {  // kPre * G <= 64: every weight is some lane's wl
+    const float w = __shfl(wl, grp + i * G, kWave);
+    acc += w * pre[i];
   }
-  for (int c0 = 0; n_seg > kPre && c0 < n_seg; c0 += 64) {
-    const float wl = (c0 + lane < n_seg) ? (c0 == 0 ? weight_of(own.x) : weight_of(ml_of(c0 + lane).x)) : 0.f;
-    const int n = min(64, n_seg - c0);
 #pragma unroll 4
-    for (int j = 0; j < n; ++j) {
-      const float w = __shfl(wl, j, kWave);
-      const float *src = ws_acc + (rec0 + (int64_t)(c0 + j) * group) * D + lane * DPL;
-#pragma unroll
-      for (int i = 0; i < DPL; ++i) acc[i] += w * src[i];
-    }
+  for (int c0 = kPre * G; c0 < n_seg; c0 += G) {  // uniform bounds: the shuffle needs every lane
+    const int c = c0 + grp;
+    const float near = __shfl(wl, c & 63, kWave);
+    if (c < n_seg) acc += (c < 64 ? near : weight_of(ml_of(c).x)) * acc_of(c);
   }
-  const float inv = L > 0.f ? 1.f / L : 0.f;
 #pragma unroll
-  for (int i = 0; i < DPL; ++i) dst[i] = f2bf(acc[i] * inv);
+  for (int s = LPR; s < kWave; s <<= 1)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] += __shfl_xor(acc[i], s, kWave);
+  if (WPR > 1) {
+    if (lane < LPR) *(f32x4 *)(part + wave * D + d) = acc;
+    __syncthreads();
+    if (!writer) return;
+#pragma unroll
+    for (int w = 1; w < WPR; ++w) acc += *(const f32x4 *)(part + w * D + d);
+  }
+  if (!writer) return;
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  u32x2 out;
+  out[0] = pack2(acc[0] * inv, acc[1] * inv);
+  out[1] = pack2(acc[2] * inv, acc[3] * inv);
+  *(u32x2 *)dst = out;
 }
 
 }  // namespace
@@ -499,13 +522,15 @@ hipError_t launch_attention(const uint16_t *qkv, int B, int n_q, int n_kv, int D
   float *ws_acc = ws;  // [records][group][D], 16-byte aligned rows
   float *ws_ml = ws_acc + (size_t)plan.records * group * D;
   int2 *ws_meta = (int2 *)(ws_ml + (size_t)plan.records * group * 2);
-  // per-sequence arrays, then two K+V page slots per wave (64 KB at D = 128)
-  const size_t lds = (((2 * (size_t)B + 1) * sizeof(int) + 15) & ~(size_t)15) + (size_t)4 * 2 * 2 * kPage * D * 2;
+  const size_t lds = attn_lds_bytes(B, D);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-  const dim3 mgrid((unsigned)(((int64_t)B * n_q + 3) / 4));
+  const int64_t rows = (int64_t)B * n_q;
+  const bool few = rows <= kMergeFewRows;
+  const dim3 mgrid((unsigned)(few ? rows : (rows + 3) / 4));
   auto go = [&](auto kflat, auto kmerge, std::atomic<uint64_t> &lds_set) {
-    if (hipError_t e = ensure_lds_limit((const void *)kflat, kMaxAttnLds, lds_set); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kflat, dim3(plan.grid), dim3(256), lds, s, qkv, n_q, n_kv, window, ctx_lens, page_table,
+    if (hipError_t e = ensure_lds_limit((const void *)kflat, attn_lds_bytes(kMaxAttnBatch, D), lds_set); e != hipSuccess)
+      return e;
+    hipLaunchKernelGGL(kflat, dim3(plan.grid), dim3(64 * attn_waves(D)), lds, s, qkv, n_q, n_kv, window, ctx_lens, page_table,
                        max_pages, ring, pool, pool_pages, plan.seg_pages, scale_log2, ws_acc, ws_ml, ws_meta, o, B);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -513,8 +538,8 @@ hipError_t launch_attention(const uint16_t *qkv, int B, int n_q, int n_kv, int D
     return hipGetLastError();
   };
   static std::atomic<uint64_t> lds_set_128{0}, lds_set_64{0};  // devices whose limit each kernel already raised
-  if (D == 128) return go(attn_flat_kernel<128>, attn_merge_kernel<128>, lds_set_128);
-  return go(attn_flat_kernel<64>, attn_merge_kernel<64>, lds_set_64);
+  if (D == 128) return go(attn_flat_kernel<128>, few ? attn_merge_kernel<128, 4> : attn_merge_kernel<128, 1>, lds_set_128);
+  return go(attn_flat_kernel<64>, few ? attn_merge_kernel<64, 4> : attn_merge_kernel<64, 1>, lds_set_64);
 }
 
 }  // namespace ods

@@ -249,16 +249,16 @@ int64_t tiled_weight_elems(int out, int in, bool gated, int groups) {
   return (int64_t)groups * tiles * (in / 64) * (128 * 64);
 }
 
-// Grid of the attention kernel: one 4-wave block per compute unit, fewer when
-// the batch cannot fill them with ranges of at least 8 pages. Fewer waves in
+// Grid of the attention kernel: one block per compute unit, fewer when the
+// batch cannot fill them with ranges of at least attn_min_pages pages. Fewer waves in
 // flight stream the pool faster: measured on one MI355X, B = 64 x U[512, 4096]
 // 122.7 -> 115.6 us, B = 256 x 8192 1444 -> 1376 us, MoE B = 512 1593 ->
 // 1563 us from three blocks per unit to one (two was in between). The kernel
 // is built for at most two waves per SIMD (256 VGPRs), which leaves its 170
 // registers unspilled.
-int attn_grid(int B, int n_kv, int span, int cus) {
-  const int64_t max_units = (int64_t)B * n_kv * span;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(std::max(cus, 1), (max_units + 31) / 32));
+int attn_grid(int B, int n_kv, int D, int span, int cus) {
+  const int64_t max_units = (int64_t)B * n_kv * span, per = (int64_t)attn_waves(D) * attn_min_pages(D);
+  return (int)std::max<int64_t>(1, std::min<int64_t>(std::max(cus, 1), (max_units + per - 1) / per));
 }
 
 int attn_span(int max_pages, int window) {
@@ -268,16 +268,15 @@ int attn_span(int max_pages, int window) {
 }
 
 AttnPlan attn_plan(int B, int n_kv, int D, int max_pages, int window, int split_pages_req, int cus) {
-  (void)D;
   const int span = attn_span(max_pages, window);
   AttnPlan plan;
   plan.seg_pages = split_pages_req;
-  plan.grid = attn_grid(B, n_kv, span, cus);
+  plan.grid = attn_grid(B, n_kv, D, span, cus);
   // Records r + seq with r a range index: ranges <= waves when S is chosen
   // from the total, else <= ceil(max units / S).
   const int64_t seqs = (int64_t)B * n_kv;
   const int64_t ranges = split_pages_req > 0 ? (seqs * span + split_pages_req - 1) / split_pages_req
-                                             : (int64_t)plan.grid * 4;
+                                             : (int64_t)plan.grid * attn_waves(D);
   plan.records = ranges + seqs;
   plan.units_ok = seqs * span < (int64_t)1 << 30;
   return plan;

@@ -88,8 +88,20 @@ struct AttnPlan {
   int64_t records;  // partial-record slots per query-head group
   bool units_ok;    // batch * n_kv * span fits the kernel's 32-bit unit index
 };
+// Fewest pages in a wave's range (when the batch cannot fill the grid): shorter
+// ranges start more waves at once, at more records to merge. Attention and
+// merge with 8, 4 and 2 pages: one 3000-token sequence of the 8B-shaped layer
+// 16.8, 14.2 and 16.4 us; the tiny layer's four of 128 tokens (64-wide heads)
+// 13.1, 11.6 and 10.6 us, eight of up to 2048 tokens 17.5, 14.3 and 14.0 us.
+constexpr int attn_min_pages(int D) { return D == 64 ? 2 : 4; }
+// Waves of an attention workgroup. A 128-wide head's page (8 KB) covers a
+// wave's own chain of loads, softmax and MFMAs at one wave per SIMD, and two
+// measured slower; a 64-wide head's page is half the bytes for the same chain,
+// and two waves per SIMD overlap it (100 sequences of up to 2048 tokens, 8 KV
+// heads: 53.0 -> 46.5 us; twice the page slots per wave instead gained nothing).
+constexpr int attn_waves(int D) { return D == 64 ? 8 : 4; }
 int attn_span(int max_pages, int window);
-int attn_grid(int B, int n_kv, int span, int cus);
+int attn_grid(int B, int n_kv, int D, int span, int cus);
 AttnPlan attn_plan(int B, int n_kv, int D, int max_pages, int window, int split_pages_req, int cus);
 size_t attn_ws_bytes(int B, int n_q, int n_kv, int D, const AttnPlan &plan);
 

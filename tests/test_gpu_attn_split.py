@@ -1,0 +1,42 @@
+"""Attention split over waves and the merge of its records, through the C ABI.
+
+Ranges of one page (split_pages = 1) leave a record per page, so the number of
+records of a row is its page count: rows with 1, 2, 5, 31 to 33 and 63 to 65
+pages and more meet every loop of the merge (the first four loads of a group,
+the loop past them, the weights past the 64th record), with rows few enough
+for four waves each and too many for that. The library's own split covers
+ranges from its shortest to several sequences long."""
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from harness import Setup, assert_close, f64, oracle_run
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():  # pragma: no cover
+    pytest.skip("no GPU", allow_module_level=True)
+
+CTX = [1, 16, 17, 80, 31 * 16, 33 * 16 - 3, 63 * 16, 64 * 16 + 1, 70 * 16 + 5]
+
+
+@pytest.mark.parametrize("split", [0, 1, 3])
+@pytest.mark.parametrize("D,n_q,n_kv,repeat", [(64, 4, 2, 1), (64, 16, 1, 5), (128, 8, 2, 1), (128, 16, 2, 5)])
+def test_attention_records(D, n_q, n_kv, repeat, split):
+    cfg = W.LayerCfg(hidden=256, n_q=n_q, n_kv=n_kv, head_dim=D, ffn=256)
+    ctx = np.array(CTX * repeat, dtype=np.int32)
+    B = len(ctx)
+    print(f"[case] attention records D {D} rows {B * n_q} split {split}", file=sys.stderr, flush=True)
+    w = W.Workload("attn_split", (cfg,), batch=B, ctx_lo=1, ctx_hi=int(ctx.max()))
+    s = Setup(w, seed=D + split, split_pages=split, ctx=ctx)
+    inp = s.oracle_inputs()
+    ref = oracle_run(inp, w.layers, 0, 5)
+    s.reset_resid()
+    s.run(0, 5)
+    torch.cuda.synchronize()
+    got = f64(s.buf("o", B, n_q * D))
+    for b in range(B):
+        assert_close(f"row {b} (context {ctx[b]})", got[b], ref["o"][b])
