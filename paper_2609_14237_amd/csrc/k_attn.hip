@@ -44,8 +44,8 @@ namespace {
 
 constexpr int kNonTemporal = 2;  // cache-policy operand of the direct-to-LDS load: nt
 constexpr int kSlots = 2;  // page slots per wave
-// Rows up to which four waves merge each (two blocks per compute unit).
-constexpr int64_t kMergeFewRows = 512;
+// Rows up to which four waves merge each (four blocks per compute unit).
+constexpr int64_t kMergeFewRows = 1024;
 // Bytes of one slot: K block, V block, and the 16 query rows of a segment that
 // starts with the page.
 constexpr int attn_slot_bytes(int D) { return 2 * kPage * D * 2 + 16 * D * 2; }
