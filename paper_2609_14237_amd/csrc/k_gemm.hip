@@ -2,15 +2,17 @@
 // expert GEMMs: C[m, n] = sum_k A[m, k] * B[n, k] (both operands K-contiguous,
 // "out x in" weights), fp32 accumulation, fused epilogues.
 //
+// Most dense GEMMs and every grouped GEMM with K a whole number of 64-wide
+// steps run elsewhere: up to 32 rows in the whole-K kernel (k_gemm_skinny.hip),
+// past that in the direct-to-LDS streaming kernel (k_gemm_stream.hip). Here are
+// the rest: K that is not a multiple of 64, outputs of at most 128 columns
+// (the router), and the split-K reduce.
+//
 // Tiling: 256 threads = 4 waves; block tile BM x BN outputs, K step BK; LDS
 // double buffering (global loads of step k+1 are in flight while step k runs
-// on the matrix cores). Decode GEMMs are weight-streaming (M <= 64 rows against
-// megabytes of weights), so the tile covers all rows it can and narrow outputs
-// are split along K to keep every compute unit streaming. Dense GEMMs past 128
-// rows, those of 33 to 64 rows but the SiLU-gated one, and the grouped expert
-// GEMMs with K % 64 = 0 go to the direct-to-LDS streaming kernel
-// (k_gemm_stream.hip); the large-M kernel here takes 64 < M <= 128 and the
-// grouped GEMMs with other K. MFMA 16x16x32 bf16: lane l holds A[m = l%16][8 k's
+// on the matrix cores). Narrow outputs are split along K to keep every compute
+// unit streaming. The large-M kernel takes dense GEMMs past 64 rows and the
+// grouped ones. MFMA 16x16x32 bf16: lane l holds A[m = l%16][8 k's
 // starting at (l/16)*8] and B[same k's][n = l%16]; the 16x16 fp32 result puts
 // rows (l/16)*4 .. +3 of column l%16 in lane l.
 #include "common.hpp"
@@ -177,8 +179,7 @@ __global__ __launch_bounds__(256) void gemm_kernel(GemmArgs p) {
   }
 }
 
-// Large-M variant (grouped expert GEMMs; dense GEMMs with 64 < M <= 128 or K
-// not a multiple of 64): 512 threads = 8 waves as 4 (M) x 2 (N), block tile
+// Large-M variant (grouped and dense GEMMs whose K is not a multiple of 64): 512 threads = 8 waves as 4 (M) x 2 (N), block tile
 // BM x BN with BN = 128 columns of B rows (SiLU: 64 gate + 64 up rows), wave
 // tile (BM/4) x 64. The whole batch fits one or two M tiles, so the weights
 // stream from HBM once. Pipeline: step k+1 arrives in registers while step k

@@ -1,9 +1,7 @@
-// Weight-streaming bf16 MFMA GEMM for M > 128 rows (the 256-row decode batch,
-// the 512-row MoE attention projections, larger prefill-sized batches), for
-// 33 to 64 rows outside the SiLU-gated FFN GEMM, and for the grouped expert
-// GEMMs (any rows per group), and for every GEMM on tiled weights (B stored
-// as the LDS image of each K step's tile, read as one contiguous run per
-// block): C[m, n] = sum_k A[m, k] * B[n, k] with the same epilogues as the
+// Weight-streaming bf16 MFMA GEMM for dense products past 32 rows, for the
+// grouped expert GEMMs (any rows per group), and for wide outputs on tiled
+// weights at any batch (B stored as the LDS image of each K step's tile, read
+// as one contiguous run per block): C[m, n] = sum_k A[m, k] * B[n, k] with the same epilogues as the
 // other GEMM kernels. Built on its own with MFMA results in
 // VGPRs (build.py passes -amdgpu-mfma-vgpr-form for this file only), which
 // keeps the accumulators in place across the K loop.

@@ -18,8 +18,7 @@ int num_cus();
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
 // Sum of split-K partials plus the epilogue (after a partial-writing launch).
 hipError_t launch_splitk_reduce(const GemmArgs &a, hipStream_t s);
-// Weight-streaming kernel (K % 64 == 0): dense GEMMs past 128 rows, of 33 to
-// 64 rows but the SiLU-gated one, grouped GEMMs, and every GEMM on tiled weights.
+// Weight-streaming kernel (K % 64 == 0): dense GEMMs past 32 rows, grouped GEMMs, and wide outputs on tiled weights.
 hipError_t launch_gemm_stream(const GemmArgs &a, hipStream_t s);
 // Whole-K kernel for up to kSkinnyRows rows (dense GEMMs, both weight layouts, splits = 1).
 hipError_t launch_gemm_skinny(const GemmArgs &a, hipStream_t s);

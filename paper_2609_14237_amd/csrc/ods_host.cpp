@@ -155,13 +155,16 @@ bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled) {
   return !large || (!b_tiled && !long_k(N, K, epi));
 }
 
-// Dense GEMMs past 128 rows, and those of 33 to 64 rows except the SiLU-gated
-// one (64-row tiles: at 64 rows qkv 20.2 -> 18.0 us, o_proj 16.4 -> 15.9 us and
-// down 31.8 -> 29.2 us on the 8B-shaped layer, gate_up level at 53 us and
-// slower below 48 rows; at 32 rows and fewer the gains are under 1 us).
+// Dense GEMMs past 32 rows whose K is a whole number of 64-wide steps (fewer
+// rows: the whole-K kernel). The register-staged kernels lose at every size
+// measured, row-major weights: the narrow layer (hidden 2048, SwiGLU 8192) at
+// 100 rows qkv 16.1 -> 10.8 us, o_proj 15.9 -> 10.9, gate_up + SiLU 25.5 -> 20.0,
+// down 25.2 -> 15.9; the 8B-shaped layer at 100 rows 24.6 -> 16.7, 20.0 -> 16.3,
+// 69.7 -> 50.9 and 38.8 -> 35.9 us, its gate_up + SiLU at 33 to 64 rows
+// 48.0-50.4 -> 43.8-48.3 us. N <= 128 (the router) has too few 128-column tiles.
 bool gemm_use_stream(int M, int N, int K, int epi) {
   if (N <= 128 || K % 64 != 0) return false;
-  return M > 128 || (M > 32 && M <= 64 && epi != EPI_SILU);
+  return M > 32;
 }
 
 namespace {

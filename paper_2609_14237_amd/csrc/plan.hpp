@@ -61,8 +61,7 @@ bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled);
 bool use_big(int M, int N);            // 64 < M: the large-M tile
 bool long_k(int N, int K, int epi);    // narrow output with K >= 2N (the down projection)
 int tile_n(int N, int K, int epi);     // decode tile width
-// Weight-streaming kernel: dense GEMMs past 128 rows, of 33 to 64 rows but
-// the SiLU-gated one, grouped GEMMs, and every GEMM on tiled weights.
+// Weight-streaming kernel: dense GEMMs past 32 rows, grouped GEMMs, and on tiled weights what the whole-K kernel leaves.
 bool gemm_use_stream(int M, int N, int K, int epi);
 int gemm_stream_rows(int M, int N, int K, int epi);  // dense block rows: 64 or 256
 int gemm_stream_splits(int M, int N, int K, int epi);
