@@ -73,6 +73,35 @@ __device__ __forceinline__ float block_sum_256(float v, float *red) {
   return t;
 }
 
+// cos and sin of the RoPE angle of dimension pair i (of D / 2) at position p:
+// p * theta^(-2 i / D), reduced mod 2 pi in double before the fp32 functions.
+__device__ __forceinline__ void rope_angle(int p, int i, int D, float theta, float &cv, float &sv) {
+  const double two_pi_hi = 6.283185307179586, two_pi_lo = 2.4492935982947064e-16;
+  const double inv = exp2(-(2.0 * i / D) * log2((double)theta));
+  const double a = (double)p * inv;
+  const double k = rint(a * (1.0 / two_pi_hi));
+  const double r = fma(-k, two_pi_lo, fma(-k, two_pi_hi, a));
+  sincosf((float)r, &sv, &cv);
+}
+
+// 8 bf16 values: their sum of squares, and their product with inv and a gain.
+__device__ __forceinline__ float sumsq8(const u32x4 &w) {
+  float t = 0.f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const float a = bf_lo(w[j]), b = bf_hi(w[j]);
+    t += a * a + b * b;
+  }
+  return t;
+}
+__device__ __forceinline__ u32x4 norm8(const u32x4 &w, const u32x4 &gw, float inv) {
+  u32x4 o;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    o[j] = pack2(bf_lo(w[j]) * inv * bf_lo(gw[j]), bf_hi(w[j]) * inv * bf_hi(gw[j]));
+  return o;
+}
+
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }
 
 }  // namespace ods

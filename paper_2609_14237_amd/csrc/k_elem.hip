@@ -8,24 +8,6 @@ namespace ods {
 
 namespace {
 
-// Sum of squares of 8 bf16 values, and their RMSNorm scaling by inv and gain.
-__device__ __forceinline__ float sumsq8(const u32x4 &w) {
-  float t = 0.f;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float a = bf_lo(w[j]), b = bf_hi(w[j]);
-    t += a * a + b * b;
-  }
-  return t;
-}
-__device__ __forceinline__ u32x4 norm8(const u32x4 &w, const u32x4 &gw, float inv) {
-  u32x4 o;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    o[j] = pack2(bf_lo(w[j]) * inv * bf_lo(gw[j]), bf_hi(w[j]) * inv * bf_hi(gw[j]));
-  return o;
-}
-
 // out[r] = x[r] * (mean(x[r]^2) + eps)^(-1/2) * gain, fp32 math, bf16 out.
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t *x, const uint16_t *gain,
                                                       uint16_t *out, int H, float eps) {
@@ -113,13 +95,8 @@ __global__ __launch_bounds__(256) void rope_append_kernel(uint16_t *qkv, int n_q
   const int qk0 = max(h0, do_rope ? 0 : n_q), qk1 = min(h1, n_q + n_kv);
   if (do_rope && qk0 < qk1) {
     if (threadIdx.x < half) {
-      const double two_pi_hi = 6.283185307179586, two_pi_lo = 2.4492935982947064e-16;
-      const double inv = exp2(-(2.0 * threadIdx.x / D) * log2((double)theta));
-      const double a = (double)p * inv;
-      const double k = rint(a * (1.0 / two_pi_hi));
-      const double r = fma(-k, two_pi_lo, fma(-k, two_pi_hi, a));
       float sv, cv;
-      sincosf((float)r, &sv, &cv);
+      rope_angle(p, threadIdx.x, D, theta, cv, sv);
       cs[threadIdx.x] = cv;
       sn[threadIdx.x] = sv;
     }

@@ -22,6 +22,10 @@ hipError_t launch_splitk_reduce(const GemmArgs &a, hipStream_t s);
 hipError_t launch_gemm_stream(const GemmArgs &a, hipStream_t s);
 // Whole-K kernel for up to kSkinnyRows rows (dense GEMMs, both weight layouts, splits = 1).
 hipError_t launch_gemm_skinny(const GemmArgs &a, hipStream_t s);
+// The same with neighbours: gain != null: A is the residual, normalised on the way in and written to xn (K at most
+// kSkinnyNormMaxK; SiLU or RoPE outputs); rope != null: bf16 qkv output rotated, k and v appended to the pool.
+hipError_t launch_gemm_skinny_fused(const GemmArgs &a, const uint16_t *gain, float eps, uint16_t *xn,
+                                    const RopeArgs *rope, hipStream_t s);
 
 hipError_t launch_rmsnorm(const uint16_t *x, const uint16_t *gain, uint16_t *out, int rows, int H,
                           float eps, hipStream_t s);

@@ -29,6 +29,9 @@ hipError_t execute(const Launch &L, hipStream_t s) {
   switch (L.kind) {
     case LK_RMSNORM: return launch_rmsnorm(L.x, L.gain, L.out, L.rows, L.width, L.eps, s);
     case LK_GEMM: return launch_gemm(L.gemm, s);
+    case LK_SKINNY:
+      return launch_gemm_skinny_fused(L.gemm, L.gain, L.eps, L.out, L.has_rope ? &L.rope : nullptr, s);
+    case LK_NONE: return hipSuccess;
     case LK_GEMM_NORM: {
       const hipError_t e = launch_gemm(L.gemm, s);
       if (e != hipSuccess) return e;

@@ -155,6 +155,15 @@ bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled) {
   return !large || (!b_tiled && !long_k(N, K, epi));
 }
 
+// Where the norm joins: up to 16 rows (past that its conversions cost as much
+// as the launch: qkv with RoPE at 24 rows of a tensor-parallel share 15.2 us
+// joined, 13.2 us apart), wide tiled outputs included (ffn_norm + gate_up + SiLU
+// of the 8B-shaped layer at 13 rows 37.5 us against 39.8 us as two launches).
+bool gemm_norm_skinny(int M, int N, int K, int epi, bool b_tiled) {
+  if (M > 16 || K > kSkinnyNormMaxK) return false;
+  return epi == EPI_SILU || gemm_use_skinny(M, N, K, epi, b_tiled);
+}
+
 // Dense GEMMs past 32 rows whose K is a whole number of 64-wide steps (fewer
 // rows: the whole-K kernel). The register-staged kernels lose at every size
 // measured, row-major weights: the narrow layer (hidden 2048, SwiGLU 8192) at
@@ -363,6 +372,32 @@ bool next_is(const ods_block *blk, int g, int op_end, OpKind k) {
   return a.layer == b.layer && b.kind == k;
 }
 
+// Operators around a whole-K GEMM that join its launch. norm_joins: g is a norm
+// and the GEMM that reads it is next in the range (qkv only with its RoPE, which
+// then joins as well). rope_joins: g is a whole-K qkv projection and RoPE is next.
+bool rope_joins(const ods_block *blk, int g, int op_end, int B) {
+  const OpRef op = op_at(blk, g);
+  if (op.kind != K_QKV || !next_is(blk, g, op_end, K_ROPE)) return false;
+  const ods_layer &L = blk->layers[op.layer];
+  return gemm_use_skinny(B, qkv_dim(L.cfg), L.cfg.hidden, EPI_BF16, tiled(L));
+}
+
+bool norm_joins(const ods_block *blk, int g, int op_end, int B) {
+  const OpRef op = op_at(blk, g);
+  const ods_layer &L = blk->layers[op.layer];
+  const ods_layer_cfg &c = L.cfg;
+  if (op.kind == K_ATTN_NORM)
+    return next_is(blk, g, op_end, K_QKV) && rope_joins(blk, g + 1, op_end, B) &&
+           gemm_norm_skinny(B, qkv_dim(c), c.hidden, EPI_BF16, tiled(L));
+  return op.kind == K_FFN_NORM && next_is(blk, g, op_end, K_GATE_UP) && next_is(blk, g + 1, op_end, K_SILU) &&
+         gemm_norm_skinny(B, c.ffn, c.hidden, EPI_SILU, tiled(L));
+}
+
+// Did the launch of an earlier operator of the range append the KV already?
+bool append_done(const ods_block *blk, int op_begin, int g, int op_end, int B) {
+  return op_at(blk, g).kind == K_KV_APPEND && g - 2 >= op_begin && rope_joins(blk, g - 2, op_end, B);
+}
+
 // The RMSNorm that reads the residual operator g writes, when it is the next
 // operator of the range: ffn_norm after o_proj_residual, or the next layer's
 // attn_norm after down_residual. Null otherwise.
@@ -537,6 +572,13 @@ void plan_launch(const ods_block *blk, int op_begin, int op_end, int i, const od
     r.do_rope = do_rope; r.do_append = do_append;
     r.partial = nullptr; r.splits = 1;
   };
+  // RoPE after the qkv projection at g_qkv, in its launch; with KV append next
+  // the append is done there too (and K_KV_APPEND's own turn is empty).
+  auto join_rope = [&](int g_qkv) {
+    rope(true, next_is(blk, g_qkv + 1, op_end, K_KV_APPEND));
+    o.has_rope = true;
+    o.kind = LK_SKINNY;
+  };
   // A residual GEMM that leaves split-K partials hands them to a kernel that
   // sums them into the residual and normalises the row at once, when the norm
   // is next in the range: one launch less (4-5 us) and one pass less over resid.
@@ -555,6 +597,25 @@ void plan_launch(const ods_block *blk, int op_begin, int op_end, int i, const od
   switch (op.kind) {
     case K_ATTN_NORM:
     case K_FFN_NORM:
+      if (norm_joins(blk, g, op_end, B)) {
+        o.kind = LK_SKINNY;
+        o.gain = U(op.kind == K_ATTN_NORM ? L.g_attn : L.g_ffn);
+        o.out = U(op.kind == K_ATTN_NORM ? st->xn : st->hn);
+        o.eps = c.rms_eps;
+        o.n_ops = 3;
+        const void *x = st->resid;
+        if (op.kind == K_ATTN_NORM) {
+          dense_gemm(x, L.w_qkv, st->qkv, qkv_dim(c), H, EPI_BF16, 0, qkv_dim(c), false, wt);
+          join_rope(g + 1);
+          o.what = "attn_norm+qkv_proj+rope";
+        } else {
+          dense_gemm(x, L.w_gate_up, st->act, c.ffn, H, EPI_SILU, c.ffn, c.ffn, false, wt);
+          o.what = "ffn_norm+gate_up+silu_mul";
+        }
+        o.gemm.splits = 1;
+        o.kind = LK_SKINNY;
+        break;
+      }
       o.kind = LK_RMSNORM;
       o.x = U(st->resid);
       o.gain = U(op.kind == K_ATTN_NORM ? L.g_attn : L.g_ffn);
@@ -564,6 +625,13 @@ void plan_launch(const ods_block *blk, int op_begin, int op_end, int i, const od
     case K_QKV: {
       // With split-K and RoPE next in the range, the RoPE / KV-append kernel
       // sums the partials itself (same order and rounding as the reduce).
+      if (rope_joins(blk, g, op_end, B)) {
+        dense_gemm(st->xn, L.w_qkv, st->qkv, qkv_dim(c), H, EPI_BF16, 0, qkv_dim(c), false, wt);
+        join_rope(g);
+        o.what = "qkv_proj+rope";
+        o.n_ops = 2;
+        break;
+      }
       const bool fuse = next_is(blk, g, op_end, K_ROPE) && gemm_splits(B, qkv_dim(c), H, EPI_BF16, wt) > 1;
       dense_gemm(st->xn, L.w_qkv, st->qkv, qkv_dim(c), H, EPI_BF16, 0, qkv_dim(c), fuse, wt);
       if (fuse) {
@@ -579,6 +647,10 @@ void plan_launch(const ods_block *blk, int op_begin, int op_end, int i, const od
     }
     case K_ROPE:
     case K_KV_APPEND: {
+      if (append_done(blk, op_begin, g, op_end, B)) {
+        o.kind = LK_NONE;
+        break;
+      }
       const bool both = op.kind == K_ROPE && next_is(blk, g, op_end, K_KV_APPEND);
       rope(op.kind == K_ROPE, both || op.kind == K_KV_APPEND);
       o.kind = LK_ROPE_APPEND;

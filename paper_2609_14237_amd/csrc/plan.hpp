@@ -56,6 +56,10 @@ constexpr int kReduceNormMaxN = 16384;
 // takes, and the dense GEMMs that go to it.
 constexpr int kSkinnyRows = 32;
 bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled);
+// The same where the RMSNorm before it joins the launch: up to 16 rows and K at
+// most kSkinnyNormMaxK (the gain's LDS), wide outputs on tiled weights as well.
+constexpr int kSkinnyNormMaxK = 7680;
+bool gemm_norm_skinny(int M, int N, int K, int epi, bool b_tiled);
 
 // Decode-tile GEMM shape choices (row-major weights).
 bool use_big(int M, int N);            // 64 < M: the large-M tile
@@ -136,7 +140,9 @@ ods_status validate_range(const ods_block *blk, int op_begin, int op_end, const 
 // One launch of a validated range.
 enum LaunchKind {
   LK_RMSNORM, LK_GEMM, LK_GEMM_NORM, LK_QKV_ROPE, LK_ROPE_APPEND, LK_ATTENTION, LK_SILU, LK_TOPK, LK_ROUTER_TOPK, LK_PERMUTE,
-  LK_COMBINE
+  LK_COMBINE,
+  LK_SKINNY,  // whole-K GEMM with the norm before it and/or RoPE and KV append after it
+  LK_NONE     // an operator an earlier launch of the range already covered
 };
 struct RopeArgs {
   uint16_t *qkv; int B, n_q, n_kv, D; float theta;
@@ -156,8 +162,9 @@ struct Launch {
   int layer;
   int n_ops;         // operators this launch covers (more than one when fused)
   const char *what;  // static name for traces and errors
-  GemmArgs gemm;     // LK_GEMM, LK_GEMM_NORM, LK_QKV_ROPE, LK_ROUTER_TOPK
-  RopeArgs rope;     // LK_QKV_ROPE, LK_ROPE_APPEND
+  GemmArgs gemm;     // LK_GEMM, LK_GEMM_NORM, LK_SKINNY, LK_QKV_ROPE, LK_ROUTER_TOPK
+  RopeArgs rope;     // LK_QKV_ROPE, LK_ROPE_APPEND, LK_SKINNY (has_rope)
+  bool has_rope;     // LK_SKINNY; with gain set, its norm's rows go to out
   AttnArgs attn;     // LK_ATTENTION
   // LK_RMSNORM: x -> out with gain; LK_GEMM_NORM: the GEMM's split-K sum into resid, then its norm -> out with gain; LK_SILU: x (gate | up) -> out; LK_COMBINE: x (yp) into out (resid)
   const uint16_t *x, *gain; uint16_t *out; int rows, width; float eps;

@@ -92,3 +92,54 @@ def test_router_against_float64(hidden, experts, batch):
     ref, slack = gemm64(s.buf("hn", batch, hidden), s.weights[0]["w_router"])
     err = ((s.buf("logits", batch, experts).double() - ref).abs() / (slack + 1e-30)).max().item()
     assert err <= 1.0, f"logits: {err:.2f} times the bound"  # fp32 output: no bf16 rounding
+
+
+@pytest.mark.parametrize("batch", [1, 8, 9, 16, 17, 32])
+@pytest.mark.parametrize("D,n_q,n_kv,hidden,tiled", [(64, 4, 2, 520, False), (128, 4, 1, 256, True),
+                                                     (128, 6, 3, 1000, False), (64, 8, 8, 7680, True),
+                                                     (128, 2, 1, 8192, False)])
+def test_norm_rope_and_append_join_qkv(D, n_q, n_kv, hidden, tiled, batch):
+    """attn_norm .. kv_append in one call: xn is the norm of the residual to one bf16 rounding (2^-8), qkv the rotated
+    products of the float64 normalised rows. Bound: each factor of a product is rounded to bf16 once (2^-9, here the
+    row before or after its 1 / rms), so a pair's two sums are off by at most 2^-8 of sum |xn||w| each with the fp32
+    sums' order, rotation adds the two, and each value is rounded to bf16 before and after it (2^-8 of their sizes).
+    The pool holds the very bits of the k and v columns in the new slots and is untouched elsewhere; hidden sizes end
+    inside a K step and reach the widest gain the launch holds and past it. Row 0 has no context: it is projected,
+    not rotated, and appends nothing."""
+    print(f"[case] norm + qkv + rope + append D {D} hidden {hidden} batch {batch}", file=sys.stderr, flush=True)
+    cfg = W.LayerCfg(hidden=hidden, n_q=n_q, n_kv=n_kv, head_dim=D, ffn=64)
+    w = W.Workload("skinny_rope", (cfg,), batch=batch, ctx_lo=1, ctx_hi=70)
+    s = Setup(w, seed=batch + D, tiled=tiled)
+    if batch > 1:
+        s.batch.ctx_lens[0] = 0
+    ctx = s.batch.ctx_lens.long()
+    s.reset_resid()
+    before = s.pools[0].clone()
+    s.run(0, 4)
+    torch.cuda.synchronize()
+    x, g = s.x.double(), s.weights[0]["g_attn"].double()
+    xn = x * torch.rsqrt((x * x).mean(-1, keepdim=True) + cfg.rms_eps) * g
+    check("xn", s.buf("xn", batch, hidden), xn, 1e-6 * xn.abs())
+    wq = s.weights[0]["w_qkv"].double()
+    heads = lambda t: t.view(batch, n_q + 2 * n_kv, D)  # noqa: E731
+    v64, mag = heads(xn @ wq.T), heads(2.0 ** -8 * (xn.abs() @ wq.abs().T))
+    half = D // 2
+    inv = cfg.rope_theta ** (-2.0 * torch.arange(half, dtype=torch.float64, device=x.device) / D)
+    ang = ((ctx - 1).clamp(min=0).double()[:, None] * inv)[:, None, :]
+    live = ((ctx > 0)[:, None, None] & (torch.arange(n_q + 2 * n_kv, device=x.device) < n_q + n_kv)[None, :, None])
+    c, sn = torch.where(live, ang.cos(), 1.0), torch.where(live, ang.sin(), 0.0)
+    a, b = v64[..., :half], v64[..., half:]
+    ref = torch.cat([a * c - b * sn, b * c + a * sn], -1)
+    both = mag[..., :half] + mag[..., half:] + (2.0 ** -8 + 1e-6) * (a.abs() + b.abs())
+    got = heads(s.buf("qkv", batch, cfg.qkv_dim))
+    check("qkv", got, ref, torch.cat([both, both], -1))
+    after = before.clone()
+    pages = s.batch.page_table.long()
+    for r in range(batch):
+        p = int(ctx[r]) - 1
+        if p < 0:
+            continue
+        page, slot = int(pages[r, p // 16]), p % 16
+        after[page, 0].view(n_kv, 16, D)[:, slot] = got[r, n_q:n_q + n_kv]
+        after[page, 1].view(n_kv, D, 16)[:, :, slot] = got[r, n_q + n_kv:]
+    assert torch.equal(s.pools[0], after)
