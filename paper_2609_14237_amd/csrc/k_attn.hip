@@ -473,11 +473,18 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float *__restrict
     const float w = __shfl(wl, grp + i * G, kWave);
     acc += w * pre[i];
   }
-#pragma unroll 4
-  for (int c0 = kPre * G; c0 < n_seg; c0 += G) {  // uniform bounds: the shuffle needs every lane
-    const int c = c0 + grp;
-    const float near = __shfl(wl, c & 63, kWave);
-    if (c < n_seg) acc += (c < 64 ? near : weight_of(ml_of(c).x)) * acc_of(c);
+  for (int c0 = kPre * G; c0 < n_seg; c0 += kPre * G) {  // uniform bounds: the shuffle needs every lane
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) {
+      const int c = c0 + grp + i * G;
+      pre[i] = c < n_seg ? acc_of(c) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int i = 0; i < kPre; ++i) {
+      const int c = c0 + grp + i * G;
+      const float near = __shfl(wl, c & 63, kWave);
+      if (c < n_seg) acc += (c < 64 ? near : weight_of(ml_of(c).x)) * pre[i];
+    }
   }
 #pragma unroll
   for (int s = LPR; s < kWave; s <<= 1)
