@@ -206,7 +206,7 @@ int stream_n_tiles(int N, int epi) { return epi == EPI_SILU ? (N + 63) / 64 : (N
 // more 256-row blocks the 256-row tile stays ahead (the 8B-shaped layer's
 // GEMMs at M = 256: gate_up 81 against 113 us, down 48-51 against 62-64 us
 // as 64-row tiles). Up to 128 rows, where two 64-row tiles stream no more rows
-// than the 256-row tile's live half, also a split grid of up to 192 256-row
+// than the 256-row tile's live half, also a split grid of fewer than 192 256-row
 // blocks gives way (down of the narrow layer, N 2048 and K 8192, at 100 rows:
 // 128 -> 256 blocks, 15.6 -> 14.6 us; qkv of a two-way tensor-parallel share at
 // 128 rows, 96 -> 192 blocks, 14.7 -> 12.9 us), and one that 64-row tiles fill
@@ -217,7 +217,7 @@ int gemm_stream_rows(int M, int N, int K, int epi) {
   if (M <= 64) return 64;
   const int tiles = (M + 255) / 256 * stream_n_tiles(N, epi);
   const int s = N % 4 != 0 ? 1 : stream_splits(tiles, K / 64);
-  if (M <= 128 && s > 1 && (tiles * s <= 192 || (K <= 2048 && 2 * tiles >= 192))) return 64;
+  if (M <= 128 && s > 1 && (tiles * s < 192 || (K <= 2048 && 2 * tiles >= 192))) return 64;
   return tiles * s < 128 ? 64 : 256;
 }
 
