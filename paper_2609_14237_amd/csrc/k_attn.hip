@@ -87,7 +87,7 @@ template <int D>
 __global__ __launch_bounds__(64 * attn_waves(D)) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_flat_kernel(
     const uint16_t *__restrict__ qkv, int n_q, int n_kv, int window, const int32_t *__restrict__ ctx_lens,
     const int32_t *__restrict__ page_table, int max_pages, int ring, const uint16_t *__restrict__ pool,
-    int64_t pool_pages, int seg_pages, float scale_log2, float *__restrict__ ws_acc, float *__restrict__ ws_ml,
+    int64_t pool_pages, int seg_pages, int n_waves, float scale_log2, float *__restrict__ ws_acc, float *__restrict__ ws_ml,
     int2 *__restrict__ ws_meta, uint16_t *__restrict__ o, int B) {
   constexpr int KK = D / 32;  // QK MFMAs per page
   constexpr int NB = D / 16;  // PV MFMAs per page
@@ -141,7 +141,8 @@ __global__ __launch_bounds__(64 * attn_waves(D)) __attribute__((amdgpu_waves_per
   constexpr int LPP = 2 * (kPage * D * 2 / 1024);  // 16-byte direct-to-LDS loads per page and lane
   uint8_t *const slots = (uint8_t *)smem_i + (((2 * B + 1) * 4 + 15) & ~15) + wave * kSlots * SLOT;
   const int total = __builtin_amdgcn_readfirstlane(s_pre[B]);
-  const int n_waves = gridDim.x * WAVES;
+  // Split over fewer waves than the grid has, the working ones spread over all workgroups.
+  const int r0 = n_waves < (int)gridDim.x * WAVES ? wave * (int)gridDim.x + (int)blockIdx.x : blockIdx.x * WAVES + wave;
   const int S = seg_pages > 0 ? seg_pages : max(attn_min_pages(D), (total + n_waves - 1) / n_waves);
   const int64_t page_stride = 2 * (int64_t)n_kv * BLK;
   const int64_t v_off = (int64_t)n_kv * BLK;
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(64 * attn_waves(D)) __attribute__((amdgpu_waves_per
     return b;
   };
 
-  for (int r = blockIdx.x * WAVES + wave; (int64_t)r * S < total; r += n_waves) {
+  for (int r = r0; (int64_t)r * S < total; r += gridDim.x * WAVES) {
     const int u0 = r * S, n_w = min(total, u0 + S) - u0;  // this range: units [u0, u0 + n_w)
 
     // Page ids of range pages [t0, t0 + 64), one per lane (-1 past the range):
@@ -532,13 +533,15 @@ hipError_t launch_attention(const uint16_t *qkv, int B, int n_q, int n_kv, int D
   const size_t lds = attn_lds_bytes(B, D);
   const float scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
   const int64_t rows = (int64_t)B * n_q;
-  const bool few = rows <= kMergeFewRows;
+  // One wave reads 4 * 256 / D records of a row in its first trip; four waves pay where rows have more on average
+  // (8-way share of the 8B-shaped layer, 1024 rows of 4 or 5 records: level or 0.5 us worse).
+  const bool few = rows <= kMergeFewRows && plan.records > (int64_t)(4 * 256 / D) * B * n_kv;
   const dim3 mgrid((unsigned)(few ? rows : (rows + 3) / 4));
   auto go = [&](auto kflat, auto kmerge, std::atomic<uint64_t> &lds_set) {
     if (hipError_t e = ensure_lds_limit((const void *)kflat, attn_lds_bytes(kMaxAttnBatch, D), lds_set); e != hipSuccess)
       return e;
     hipLaunchKernelGGL(kflat, dim3(plan.grid), dim3(64 * attn_waves(D)), lds, s, qkv, n_q, n_kv, window, ctx_lens, page_table,
-                       max_pages, ring, pool, pool_pages, plan.seg_pages, scale_log2, ws_acc, ws_ml, ws_meta, o, B);
+                       max_pages, ring, pool, pool_pages, plan.seg_pages, plan.waves, scale_log2, ws_acc, ws_ml, ws_meta, o, B);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kmerge, mgrid, dim3(256), 0, s, ws_acc, ws_ml, ws_meta, n_q, n_kv, ctx_lens, o, B);

@@ -120,6 +120,15 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
   const int s_begin = split * per;
   const int nk = min(per, steps - s_begin);  // may be <= 0 for a trailing split: it writes zeros
   const int last = max(nk - 1, 0);
+  // Blocks of different weight tiles start at different K steps where each tile
+  // is read by one block over all of K: tiles and rows lie powers of two apart,
+  // and in step the blocks would ask the same HBM channels. Dense FFN stage of
+  // the 8B-shaped layer: 64 rows, row-major weights 83.2 -> 76.3 us; 256 rows,
+  // tiled 121.5 -> 117.5, row-major 125.1 -> 119.8. Where M tiles share a weight
+  // tile, or the blocks an A slice, through L2, they must stay in step (2048
+  // rows 634 -> 820 us), and split-K ranges are too short to differ (qkv at 256
+  // rows 25.0 -> 26.1 us).
+  const int rot = p.group_off || p.splits > 1 || m_tiles > 1 || nk <= 0 ? 0 : nt % nk;
 
   // Load q fills LDS row 8q + lane / 8 of its tile, position lane % 8, with
   // chunk c = (lane % 8) ^ (row % 8) of that row, so chunk c of row r sits at
@@ -181,7 +190,9 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
       constexpr bool NT = decltype(nt_c)::value;  // weight loads with the non-temporal policy
       constexpr int LW = LIVE ? LOADS : BL;  // loads per step of this wave
       auto issue = [&](int t, int slot) {
-        const int64_t k = (int64_t)t * BK;  // t <= last
+        int kt = t + rot;  // t <= last
+        kt = kt >= nk ? kt - nk : kt;
+        const int64_t k = (int64_t)kt * BK;
         if (LIVE) {
 #pragma unroll
           for (int q = 0; q < AL; ++q)
@@ -192,7 +203,7 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
 #pragma unroll
         for (int q = 0; q < BL; ++q)
           __builtin_amdgcn_global_load_lds(
-              (const void *)(bptr[q] + t * bstep),
+              (const void *)(bptr[q] + kt * bstep),
               (__attribute__((address_space(3))) void *)(lds_b + slot * BSTAGE + (wave * BL + q) * 1024), 16, 0,
               NT ? kNonTemporal : 0);
       };

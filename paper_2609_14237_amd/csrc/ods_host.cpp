@@ -292,11 +292,19 @@ AttnPlan attn_plan(int B, int n_kv, int D, int max_pages, int window, int split_
   AttnPlan plan;
   plan.seg_pages = split_pages_req;
   plan.grid = attn_grid(B, n_kv, D, span, cus);
+  plan.waves = plan.grid * attn_waves(D);
+  // From 6144 (sequence, KV head) pairs the waves stay what four per workgroup
+  // and ranges of at least 8 pages give: so many pairs fill the chip anyway,
+  // and their records are most of the workspace, which must not outgrow what a
+  // fixed one (the library's own scratch) was enough for.
+  if ((int64_t)B * n_kv >= 6144)
+    plan.waves = (int)std::min<int64_t>(plan.waves, 4 * std::min<int64_t>(std::max(cus, 1),
+                                                                          ((int64_t)B * n_kv * span + 31) / 32));
   // Records r + seq with r a range index: ranges <= waves when S is chosen
   // from the total, else <= ceil(max units / S).
   const int64_t seqs = (int64_t)B * n_kv;
   const int64_t ranges = split_pages_req > 0 ? (seqs * span + split_pages_req - 1) / split_pages_req
-                                             : (int64_t)plan.grid * attn_waves(D);
+                                             : (int64_t)plan.waves;
   plan.records = ranges + seqs;
   plan.units_ok = seqs * span < (int64_t)1 << 30;
   return plan;

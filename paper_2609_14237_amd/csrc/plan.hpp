@@ -88,6 +88,7 @@ constexpr int kMaxAttnBatch = 4096;  // the kernel keeps per-sequence contexts a
 struct AttnPlan {
   int seg_pages;    // pages per wave range; 0: total / waves (at least 8)
   int grid;         // workgroups of the attention kernel
+  int waves;        // waves the units are split over (at most grid * attn_waves)
   int64_t records;  // partial-record slots per query-head group
   bool units_ok;    // batch * n_kv * span fits the kernel's 32-bit unit index
 };

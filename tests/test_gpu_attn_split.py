@@ -24,7 +24,7 @@ CTX = [1, 16, 17, 80, 31 * 16, 33 * 16 - 3, 63 * 16, 64 * 16 + 1, 70 * 16 + 5]
 
 
 @pytest.mark.parametrize("split", [0, 1, 3])
-@pytest.mark.parametrize("D,n_q,n_kv,repeat", [(64, 4, 2, 1), (64, 16, 1, 5), (128, 8, 2, 1), (128, 16, 2, 5)])
+@pytest.mark.parametrize("D,n_q,n_kv,repeat", [(64, 4, 2, 1), (64, 16, 1, 8), (128, 8, 2, 1), (128, 16, 2, 8)])
 def test_attention_records(D, n_q, n_kv, repeat, split):
     cfg = W.LayerCfg(hidden=256, n_q=n_q, n_kv=n_kv, head_dim=D, ffn=256)
     ctx = np.array(CTX * repeat, dtype=np.int32)
