@@ -274,16 +274,15 @@ __global__ __launch_bounds__(64 * W) void gemm_skinny_kernel(GemmArgs p, SkinnyF
   }
   // Slices of 64 values of a row (whole cache lines) go round the blocks, eight threads each.
   const int slices = (p.K + 63) / 64;
-  auto slice_of = [&](int it, int &m, int &k) {  // this thread's 8 values of its it-th slice; false past the end
+  auto slice_of = [&](int it, int &m, int &k) {  // this thread's 8 values of its it-th slice; false past the last slice
     const int u = blockIdx.x + gridDim.x * ((tid >> 3) + it * 8 * W);
     m = u / slices;
-    k = u % slices * 64 + (tid & 7) * 8;
-    return m < p.M && k < p.K;
+    k = u % slices * 64 + (tid & 7) * 8;  // K or more: past the end of a row's last, short slice; later slices may follow
+    return m < p.M;
   };
   u32x4 xs = {0u, 0u, 0u, 0u};
   int xm, xk;
-  const bool x_any = NORM && slice_of(0, xm, xk);
-  if (x_any) xs = *(const u32x4 *)(p.A + (int64_t)xm * p.lda + xk);
+  if (NORM && slice_of(0, xm, xk) && xk < p.K) xs = *(const u32x4 *)(p.A + (int64_t)xm * p.lda + xk);
 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   for (; i < cnt; ++i) {
@@ -365,6 +364,7 @@ __global__ __launch_bounds__(64 * W) void gemm_skinny_kernel(GemmArgs p, SkinnyF
   }
   if (NORM) {
     for (int it = 0; slice_of(it, xm, xk); ++it) {
+      if (xk >= p.K) continue;
       if (it > 0) xs = *(const u32x4 *)(p.A + (int64_t)xm * p.lda + xk);
       const u32x4 g = *(const u32x4 *)(gain_lds + xk * 2);
       *(u32x4 *)(fu.xn + (int64_t)xm * p.K + xk) = norm8(xs, g, inv_of(xm));

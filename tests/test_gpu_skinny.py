@@ -94,9 +94,36 @@ def test_router_against_float64(hidden, experts, batch):
     assert err <= 1.0, f"logits: {err:.2f} times the bound"  # fp32 output: no bf16 rounding
 
 
+@pytest.mark.parametrize("batch", [1, 8, 9, 16])
+@pytest.mark.parametrize("hidden,ffn", [(2056, 64), (520, 16), (4104, 128)])
+def test_norm_joins_gate_up(hidden, ffn, batch):
+    """ffn_norm, gate_up and SiLU in one call: hn is the norm of the residual to one bf16 rounding (2^-8), act the gated
+    products of the float64 normalised rows. Bound: each factor of a product is rounded to bf16 once (2^-9, here the row
+    before or after its 1 / rms), so a sum is off by at most 2^-8 of sum |hn||w| with the fp32 order; SiLU(gate) * up
+    carries both through (sensitivities at most 1.1 |up| and |silu|) and is rounded once. Few blocks against rows whose
+    last 64-wide slice is short: every thread writes several slices of hn, with short ones among them."""
+    print(f"[case] norm + gate_up + SiLU hidden {hidden} ffn {ffn} batch {batch}", file=sys.stderr, flush=True)
+    cfg = W.LayerCfg(hidden=hidden, n_q=2, n_kv=1, head_dim=64, ffn=ffn)
+    s = Setup(W.Workload("skinny_norm", (cfg,), batch=batch, ctx_lo=1, ctx_hi=20), seed=batch + hidden)
+    s.reset_resid()
+    s.run(6, 9)
+    torch.cuda.synchronize()
+    x, g = s.x.double(), s.weights[0]["g_ffn"].double()
+    hn = x * torch.rsqrt((x * x).mean(-1, keepdim=True) + cfg.rms_eps) * g
+    check("hn", s.buf("hn", batch, hidden), hn, 1e-6 * hn.abs())
+    w = s.weights[0]["w_gate_up"].double()
+    gu, mag = hn @ w.T, 2.0 ** -8 * (hn.abs() @ w.abs().T)
+    gate, up = gu[:, :ffn], gu[:, ffn:]
+    act = torch.nn.functional.silu(gate)
+    check("act", s.buf("act", batch, ffn), act * up,
+          1.1 * up.abs() * mag[:, :ffn] + act.abs() * mag[:, ffn:] + 1.1 * mag[:, :ffn] * mag[:, ffn:]
+          + 1e-6 * (act * up).abs())
+
+
 @pytest.mark.parametrize("batch", [1, 8, 9, 16, 17, 32])
 @pytest.mark.parametrize("D,n_q,n_kv,hidden,tiled", [(64, 4, 2, 520, False), (128, 4, 1, 256, True),
                                                      (128, 6, 3, 1000, False), (64, 8, 8, 7680, True),
+                                                     (64, 1, 1, 2056, False),
                                                      (128, 2, 1, 8192, False)])
 def test_norm_rope_and_append_join_qkv(D, n_q, n_kv, hidden, tiled, batch):
     """attn_norm .. kv_append in one call: xn is the norm of the residual to one bf16 rounding (2^-8), qkv the rotated
