@@ -206,7 +206,11 @@ size_t ods_kv_pool_bytes(const ods_layer_cfg *cfg, int64_t pool_pages);
  * over the block's layers; 0 when no layer uses the buffer). */
 size_t ods_live_bytes(const ods_block *blk, int32_t batch, ods_buffer which);
 
-/* Minimum ods_state.ws_bytes for any operator range of this block and batch. */
+/* Minimum ods_state.ws_bytes for any operator range of this block and batch,
+ * under the launch plans of the library that is loaded: ask it again after an
+ * update instead of carrying a size over. A larger batch does not always need
+ * more, so one workspace for several batch sizes takes the largest of their
+ * needs. */
 size_t ods_workspace_bytes(const ods_block *blk, const ods_batch *batch);
 
 /* Number of operators of the block (sum over layers of 10 or 14); < 0 on error. */

@@ -80,7 +80,12 @@ size_t layer_ws_bytes(const ods_layer &L, const ods_batch *b, int cus) {
   const int B = b->batch;
   const bool t = tiled(L);
   size_t w = align_up(attn_ws_bytes(B, c.n_q, c.n_kv, c.head_dim, plan_for(c, b, cus)));
-  auto g = [&](int N, int K, int epi, bool bt) { w = std::max(w, align_up(gemm_partial_bytes(B, N, K, epi, bt))); };
+  // A batch of 65 to 128 rows also covers 64, whose split-K may be the larger
+  // one (a SiLU-gated GEMM that runs unsplit past 64 rows).
+  auto g = [&](int N, int K, int epi, bool bt) {
+    w = std::max(w, align_up(gemm_partial_bytes(B, N, K, epi, bt)));
+    if (B > 64 && B <= 128) w = std::max(w, align_up(gemm_partial_bytes(64, N, K, epi, bt)));
+  };
   g(qkv_dim(c), c.hidden, EPI_BF16, t);
   g(c.hidden, c.n_q * c.head_dim, EPI_RESID, t);
   if (is_moe(c)) {
@@ -293,16 +298,18 @@ AttnPlan attn_plan(int B, int n_kv, int D, int max_pages, int window, int split_
   plan.seg_pages = split_pages_req;
   plan.grid = attn_grid(B, n_kv, D, span, cus);
   plan.waves = plan.grid * attn_waves(D);
-  // From 6144 (sequence, KV head) pairs the waves stay what four per workgroup
-  // and ranges of at least 8 pages give: so many pairs fill the chip anyway,
-  // and their records are most of the workspace, which must not outgrow what a
-  // fixed one (the library's own scratch) was enough for.
-  if ((int64_t)B * n_kv >= 6144)
-    plan.waves = (int)std::min<int64_t>(plan.waves, 4 * std::min<int64_t>(std::max(cus, 1),
-                                                                          ((int64_t)B * n_kv * span + 31) / 32));
+  // The records are most of the workspace, which must neither outgrow what a
+  // fixed one (the library's own scratch) is enough for nor shrink as the batch
+  // grows (a workspace sized for the largest batch serves the smaller ones). So
+  // past 6143 (sequence, KV head) pairs, which fill the chip anyway, the waves
+  // make room for the pairs' records, down to what four per workgroup and
+  // ranges of at least 8 pages give.
+  const int64_t seqs = (int64_t)B * n_kv;
+  const int64_t least = 4 * std::min<int64_t>(std::max(cus, 1), (seqs * span + 31) / 32);
+  const int64_t room = (int64_t)std::max(cus, 1) * attn_waves(D) + 6143 - seqs;
+  plan.waves = (int)std::min<int64_t>(plan.waves, std::max(least, room));
   // Records r + seq with r a range index: ranges <= waves when S is chosen
   // from the total, else <= ceil(max units / S).
-  const int64_t seqs = (int64_t)B * n_kv;
   const int64_t ranges = split_pages_req > 0 ? (seqs * span + split_pages_req - 1) / split_pages_req
                                              : (int64_t)plan.waves;
   plan.records = ranges + seqs;

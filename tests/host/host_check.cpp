@@ -296,6 +296,41 @@ static void check_random_shapes() {
   }
 }
 
+// A workspace sized for a batch serves the smaller ones: attention's records
+// never shrink as the batch grows, and neither do the needs of a layer all of
+// attention (no split-K) and of one whose SiLU-gated GEMM splits K up to 64
+// rows and runs unsplit at 65 to 128.
+static void check_workspace_growth() {
+  for (int D : {64, 128})
+    for (int n_kv : {1, 2, 8})
+      for (int max_pages : {1, 2, 8, 200})
+        for (int window : {0, 100}) {
+          size_t last = 0;
+          for (int B = 1; B <= 4096; ++B) {
+            const AttnPlan p = attn_plan(B, n_kv, D, max_pages, window, 0, 256);
+            CHECK(p.waves >= 1 && p.waves <= p.grid * attn_waves(D));
+            const size_t w = attn_ws_bytes(B, 4 * n_kv, n_kv, D, p);
+            CHECK(w >= last);
+            CHECK(w <= ODS_SCRATCH_BYTES || (int64_t)B * n_kv > 6143);
+            last = w;
+          }
+        }
+  ods_layer L;
+  memset(&L, 0, sizeof(L));
+  const ods_block blk{1, &L};
+  auto need = [&](int B) {
+    const ods_batch batch{B, 8, nullptr, nullptr, 0, 0, nullptr};
+    return block_ws_bytes(&blk, &batch, 256);
+  };
+  L.cfg = ods_layer_cfg{256, 4, 2, 64, 688, 0, 0, 0, 0, 10000.f, 1e-6f};
+  for (int B = 1; B < 4096; ++B) CHECK(need(B) <= need(B + 1));
+  for (int tiled = 0; tiled < 2; ++tiled) {
+    L.weight_layout = tiled ? ODS_WEIGHTS_TILED : ODS_WEIGHTS_ROWS;
+    L.cfg = ods_layer_cfg{2048, 32, 8, 64, 8192, 0, 0, 0, 0, 10000.f, 1e-6f};
+    for (int B = 33; B < 128; ++B) CHECK(need(B) <= need(B + 1));
+  }
+}
+
 int main(int argc, char **argv) {
   if (argc < 2) {
     fprintf(stderr, "usage: host_check workloads.txt\n");
@@ -305,6 +340,7 @@ int main(int argc, char **argv) {
   check_bad_configs();
   check_stream_tiles();
   check_random_shapes();
+  check_workspace_growth();
   for (Work &w : read_works(argv[1])) {
     for (int tiled = 0; tiled < 2; ++tiled) {
       for (ods_layer &L : w.layers) L.weight_layout = tiled ? ODS_WEIGHTS_TILED : ODS_WEIGHTS_ROWS;
