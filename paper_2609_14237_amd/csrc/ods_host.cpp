@@ -211,18 +211,27 @@ int stream_n_tiles(int N, int epi) { return epi == EPI_SILU ? (N + 63) / 64 : (N
 // more 256-row blocks the 256-row tile stays ahead (the 8B-shaped layer's
 // GEMMs at M = 256: gate_up 81 against 113 us, down 48-51 against 62-64 us
 // as 64-row tiles). Up to 128 rows, where two 64-row tiles stream no more rows
-// than the 256-row tile's live half, also a split grid of fewer than 192 256-row
-// blocks gives way (down of the narrow layer, N 2048 and K 8192, at 100 rows:
-// 128 -> 256 blocks, 15.6 -> 14.6 us; qkv of a two-way tensor-parallel share at
-// 128 rows, 96 -> 192 blocks, 14.7 -> 12.9 us), and one that 64-row tiles fill
-// without split-K over a short K (gate_up + SiLU of the narrow layer, N 8192 and
-// K 2048, at 100 rows 20.1 -> 14.3 us, partials and reduce gone; at K 4096 the
-// two are level, 33.1 against 31.3 us at 70 rows and 35.5 against 37.3 at 128).
+// than the 256-row tile's live half, 64-row tiles also take
+//  - a split 256-row grid of fewer than 192 blocks, if they make more blocks of
+//    it (down of the narrow layer, N 2048 and K 8192, at 100 rows: 128 -> 256
+//    blocks, 15.6 -> 14.6 us; o_proj of a two-way share, N 4096 and K 2048, at
+//    128 rows 13.3 -> 12.2 us). At the same number of blocks, half the split,
+//    they lose (N 5120, 160 blocks both ways: K 13824 at 65 rows 35.1 against
+//    48.6 us; N 10240 and K 8192 30.1 against 37.9 us);
+//  - a split grid that they fill without split-K over a short K (gate_up + SiLU
+//    of the narrow layer, N 8192 and K 2048, at 100 rows 22.1 -> 19.7 us,
+//    partials and reduce gone; N 6144 19.4 -> 18.4). At K 2560 the two are level
+//    (N 6144 at 65 to 128 rows 20.2-24.7 and 21.3-23.4 us), at K 3584
+//    they lose (N 6144 at 65 rows 24.4 against 28.4 us, at 128 rows 29.1
+//    against 30.3 us).
 int gemm_stream_rows(int M, int N, int K, int epi) {
   if (M <= 64) return 64;
   const int tiles = (M + 255) / 256 * stream_n_tiles(N, epi);
   const int s = N % 4 != 0 ? 1 : stream_splits(tiles, K / 64);
-  if (M <= 128 && s > 1 && (tiles * s < 192 || (K <= 2048 && 2 * tiles >= 192))) return 64;
+  if (M <= 128 && s > 1) {
+    const int blocks64 = 2 * tiles * stream_splits(2 * tiles, K / 64);
+    if ((tiles * s < 192 && blocks64 > tiles * s) || (K <= 2048 && 2 * tiles >= 192)) return 64;
+  }
   return tiles * s < 128 ? 64 : 256;
 }
 

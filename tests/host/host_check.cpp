@@ -237,6 +237,13 @@ static void check_stream_tiles() {
       {64, 14336, 4096, EPI_SILU, 64, 1},   {64, 4096, 4096, EPI_RESID, 64, 8},
       {512, 4096, 4096, EPI_RESID, 256, 4}, {512, 5120, 4096, EPI_BF16, 256, 2},
       {200, 9000, 512, EPI_SILU, 256, 1},   {200, 896, 640, EPI_BF16, 64, 1},
+      // 65 to 128 rows: 64-row tiles where they make more blocks, or none of the split over a short K
+      {100, 2048, 8192, EPI_RESID, 64, 8},  {128, 4096, 2048, EPI_RESID, 64, 4},
+      {100, 8192, 2048, EPI_SILU, 64, 1},   {100, 6144, 2048, EPI_SILU, 64, 1},
+      {65, 5120, 13824, EPI_RESID, 256, 4}, {128, 5120, 5120, EPI_RESID, 256, 4},
+      {100, 10240, 8192, EPI_BF16, 256, 2}, {128, 9216, 7168, EPI_BF16, 256, 2},
+      {65, 5120, 3072, EPI_BF16, 256, 4},   {128, 5504, 2048, EPI_SILU, 256, 2},
+      {100, 8192, 4096, EPI_SILU, 256, 2},
   };
   for (const Case &c : cases) {
     CHECK(gemm_stream_rows(c.M, c.N, c.K, c.epi) == c.rows);
