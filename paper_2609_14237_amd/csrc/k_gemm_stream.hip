@@ -54,8 +54,9 @@ constexpr int kStageRow = 132;
 // (split-K) and the M tiles of one weight slab run on one XCD at the same
 // time, so A slices and weight slabs are served by that XCD's L2. This file
 // is built with MFMA results in VGPRs, which keeps the accumulators in place.
-// MG = 64-row M groups per block (4, 2 or 1, above); NSLOT = K steps of LDS.
-template <int MG, int NSLOT, int EPI, bool PARTIAL>
+// MG = 64-row M groups per block (4, 2 or 1, above); NSLOT = K steps of LDS;
+// STAGGER: gemm_stagger, below.
+template <int MG, int NSLOT, int EPI, bool PARTIAL, bool STAGGER>
 __global__ __launch_bounds__(MG == 4 ? 512 : 256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
   constexpr int BK = 64, BNR = 128;
@@ -120,15 +121,7 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
   const int s_begin = split * per;
   const int nk = min(per, steps - s_begin);  // may be <= 0 for a trailing split: it writes zeros
   const int last = max(nk - 1, 0);
-  // Blocks of different weight tiles start at different K steps where each tile
-  // is read by one block over all of K: tiles and rows lie powers of two apart,
-  // and in step the blocks would ask the same HBM channels. Dense FFN stage of
-  // the 8B-shaped layer: 64 rows, row-major weights 83.2 -> 76.3 us; 256 rows,
-  // tiled 121.5 -> 117.5, row-major 125.1 -> 119.8. Where M tiles share a weight
-  // tile, or the blocks an A slice, through L2, they must stay in step (2048
-  // rows 634 -> 820 us), and split-K ranges are too short to differ (qkv at 256
-  // rows 25.0 -> 26.1 us).
-  const int rot = p.group_off || p.splits > 1 || m_tiles > 1 || nk <= 0 ? 0 : nt % nk;
+  const int rot = STAGGER ? nt % nk : 0;  // K step this block starts at (STAGGER: nk > 0)
 
   // Load q fills LDS row 8q + lane / 8 of its tile, position lane % 8, with
   // chunk c = (lane % 8) ^ (row % 8) of that row, so chunk c of row r sits at
@@ -191,7 +184,7 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
       constexpr int LW = LIVE ? LOADS : BL;  // loads per step of this wave
       auto issue = [&](int t, int slot) {
         int kt = t + rot;  // t <= last
-        kt = kt >= nk ? kt - nk : kt;
+        if (STAGGER) kt = kt >= nk ? kt - nk : kt;
         const int64_t k = (int64_t)kt * BK;
         if (LIVE) {
 #pragma unroll
@@ -284,10 +277,10 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
     };
     if (nk > 0) {
       if (live) {
-        if (b_once) pipeline(std::true_type{}, std::true_type{});
+        if (STAGGER || b_once) pipeline(std::true_type{}, std::true_type{});
         else pipeline(std::true_type{}, std::false_type{});
       } else {
-        if (b_once) pipeline(std::false_type{}, std::true_type{});
+        if (STAGGER || b_once) pipeline(std::false_type{}, std::true_type{});
         else pipeline(std::false_type{}, std::false_type{});
       }
     }
@@ -423,14 +416,14 @@ void gemm_stream_kernel(GemmArgs p, int n_tiles, int m_tiles) {
   }
 }
 
-template <int MG, int NSLOT, int EPI, bool PARTIAL>
+template <int MG, int NSLOT, int EPI, bool PARTIAL, bool STAGGER = false>
 hipError_t launch_stream(const GemmArgs &a, hipStream_t s) {
   constexpr int BN = EPI == EPI_SILU ? 64 : 128;
   const int n_tiles = (a.N + BN - 1) / BN, m_tiles = (a.M + 64 * MG - 1) / (64 * MG);
   const int g = 8 / a.splits;  // splits is 1, 2, 4 or 8 (gemm_stream_splits)
   // dense: a 1-D grid placed on the XCDs; grouped: (N tile, group)
   const dim3 grid = a.group_off ? dim3(n_tiles, a.groups) : dim3(8 * m_tiles * ((n_tiles + g - 1) / g));
-  auto kern = gemm_stream_kernel<MG, NSLOT, EPI, PARTIAL>;
+  auto kern = gemm_stream_kernel<MG, NSLOT, EPI, PARTIAL, STAGGER>;
   // per slot: B tile + A tile per M group; at least the epilogue's fp32 tile
   const size_t lds = std::max<size_t>((size_t)NSLOT * (128 * 64 * 2 + MG * 64 * 64 * 2), (size_t)64 * MG * kStageRow * 4);
   static std::atomic<uint64_t> lds_set{0};  // devices whose limit this kernel already raised
@@ -463,8 +456,35 @@ StreamTile gemm_stream_tile(const GemmArgs &a) {
   return gemm_stream_rows(a.M, a.N, a.K, a.epi) == 64 ? TILE_64 : TILE_256;
 }
 
+// Blocks of different weight tiles start at different K steps where each tile
+// is read by one block over all of K: weight rows and tiles lie a power of two
+// apart, or nearly, and in step the blocks would ask the same HBM channels.
+// In step -> staggered:
+//  - 64-row tile, K a multiple of 2048: FFN stage at 64 rows, row-major K 6144
+//    129.3 -> 122.5 us, K 8192 250 -> 238, norm + gate_up + SiLU at K 4096 50.4
+//    -> 44.9; tiled K 6144 117.9 -> 110.8, K 4096 level. Other K lose a little
+//    (gate_up + SiLU at K 5120, tiled 50.3 -> 51.1, row-major 53.3 -> 54.4).
+//  - 256-row tile: FFN stage at 256 rows, tiled, K 4096 114.3 -> 108.9 us, K 5120
+//    146.3 -> 141.7, K 6144 169.0 -> 164.0; row-major K 5120 at 192 rows 138.6 ->
+//    135.0; K 3584 and 7168 level.
+//  - Tiled weights of more K or more tiles lose: gate_up + SiLU at 64 rows, K
+//    8192, 224 tiles 72.7 -> 81.3 us, 448 tiles 146 -> 168; at 256 rows K 7168,
+//    288 tiles 191 -> 195, K 3584, 296 tiles 102.2 -> 104.5.
+// Where M tiles share a weight tile, or the blocks an A slice, through L2, they
+// must stay in step (2048 rows 634 -> 820 us), and split-K ranges are too short
+// to differ (qkv at 256 rows 25.0 -> 26.1 us). A kernel of its own: the wrapped
+// step index, or its code beside the plain loop's, costs every other GEMM 1-4%.
+bool gemm_stagger(const GemmArgs &a, int rows) {
+  if (a.group_off || a.splits > 1 || a.M > rows) return false;
+  if (rows == 64 && a.K % 2048 != 0) return false;
+  const int n_tiles = a.epi == EPI_SILU ? (a.N + 63) / 64 : (a.N + 127) / 128;
+  return !a.b_tiled || (n_tiles <= 256 && a.K <= 6144);
+}
+
 template <int MG, int NSLOT, int EPI>
 hipError_t launch_part(const GemmArgs &a, hipStream_t s) {
+  if constexpr (MG != 2)
+    if (gemm_stagger(a, 64 * MG)) return launch_stream<MG, NSLOT, EPI, false, true>(a, s);
   return a.splits > 1 ? launch_stream<MG, NSLOT, EPI, true>(a, s) : launch_stream<MG, NSLOT, EPI, false>(a, s);
 }
 
