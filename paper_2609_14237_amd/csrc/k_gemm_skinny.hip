@@ -102,9 +102,12 @@ __global__ __launch_bounds__(64 * W) void gemm_skinny_kernel(GemmArgs p, SkinnyF
   const int steps = (p.K + 63) / 64;
   const int cnt = (steps - wave + W - 1) / W;  // K steps wave, wave + W, ...
   uint8_t *const ring = smem + wave * NS * SLOT;
-  // Blocks of different weight tiles start at different K steps: tiles lie a
-  // power of two apart, and in step they would ask the same HBM channels.
-  const int rot = (n0 >> (SILU ? 6 : 7)) % steps;
+  // Blocks of different weight tiles start at different K steps: rows and tiles
+  // lie a power of two apart, and in step they would ask the same HBM channels
+  // (13 rows, row-major, K 8192: o_proj 28.1 -> 22.3 us, gate_up + SiLU 171 ->
+  // 147; K 4096 42.5 -> 35.8). Tiles that do not lie so stay in step (K 7168, 8
+  // rows: o_proj 17.9 -> 16.8 us, norm + gate_up + SiLU 110 -> 104).
+  const int rot = TILED && p.K % 2048 != 0 ? 0 : (n0 >> (SILU ? 6 : 7)) % steps;
   auto step_of = [&](int i) {  // K step of this wave's turn i < cnt
     const int s = wave + i * W + rot;
     return s >= steps ? s - steps : s;
