@@ -144,9 +144,19 @@ int tile_n(int N, int K, int epi) {
 //    8192): the streaming kernel's blocks already read such a weight as long
 //    runs, without split-K (gate_up + SiLU of the 8B-shaped layer at 13 rows
 //    37.1 us there, 37.7 us here; row-major weights 47.7 -> 36.7 us);
-//  - from 17 rows, where a block reads twice the activation rows, narrow
-//    outputs (the router: its split-K sums fuse into top-k, 14.8 us both ways)
-//    and, past 32M elements, tiled weights and long K (down: tiled 25.7 us both
+//  - tiled weights of 64M elements and more with K a multiple of 8192 and N of
+//    4096: a block's 2- or 4-KB slices of its tiles then fall on few HBM
+//    channels (N and K 8192 at 1 row 24.8 us there, 28-35 here by where the
+//    weight lies; N 4096 and K 16384 26.2 and 27.0-28.7);
+//  - tiled weights past 8 rows with K past 16384 on fewer than 4096 columns,
+//    where 16 to 192 blocks each stream a long K alone (N 2048 and K 28672 at 16
+//    rows 33.0 there, 35.5 here; at 8 rows 32.5 and 30.4);
+//  - from 17 rows, where a block reads twice the activation rows: narrow outputs
+//    (the router: its split-K sums fuse into top-k, 14.8 us both ways); up to
+//    32M elements, long K (N 2048: tiled, K 8192 at 24 rows 15.4 there and 14.8
+//    here, at 32 15.9 and 16.3, K 12288 at 24 19.4 and 20.5; row-major, K 8192
+//    at 32 rows 16.8 and 15.5, K 12288 at 24 20.9 and 21.0, at 32 20.9 and
+//    23.7); and, past 32M elements, tiled weights and long K (down: tiled 25.7 us both
 //    ways at 24 rows, 25.9 there and 27.9 here at 32; row-major 27.3 there and
 //    29.4 here at 32). Smaller ones gain the partials and the reduce (o_proj at
 //    24 rows 14.0 -> 9.5 us), wide row-major ones the whole-line loads (gate_up
@@ -154,10 +164,13 @@ int tile_n(int N, int K, int epi) {
 bool gemm_use_skinny(int M, int N, int K, int epi, bool b_tiled) {
   if (M > kSkinnyRows) return false;
   if (b_tiled && N > (epi == EPI_SILU ? 4096 : 8192)) return false;
-  if (M <= 16) return true;
+  const int64_t elems = (int64_t)N * K * (epi == EPI_SILU ? 2 : 1);
+  if (b_tiled && elems >= (int64_t)64 << 20 && K % 8192 == 0 && N % 4096 == 0) return false;
+  if (M <= 16) return !(b_tiled && M > 8 && K > 16384 && N < 4096);
   if (N <= 128) return false;
-  const bool large = (int64_t)N * K * (epi == EPI_SILU ? 2 : 1) > (int64_t)32 << 20;
-  return !large || (!b_tiled && !long_k(N, K, epi));
+  if (elems > (int64_t)32 << 20) return !b_tiled && !long_k(N, K, epi);
+  if (!b_tiled) return K <= (M <= 24 ? 16384 : 8192);
+  return K < 8192 || (K == 8192 && (M <= 24 || N >= 3072));
 }
 
 // Where the norm joins: up to 16 rows (past that its conversions cost as much

@@ -303,6 +303,28 @@ static void check_random_shapes() {
   }
 }
 
+// Where the whole-K kernel runs, at the shapes both kernels were measured on.
+static void check_skinny_rule() {
+  struct Case {
+    int M, N, K, epi;
+    bool tiled, skinny;
+  };
+  const Case cases[] = {
+      {1, 8192, 8192, EPI_RESID, true, false},   {16, 8192, 8192, EPI_RESID, true, false},
+      {1, 4096, 16384, EPI_RESID, true, false},  {13, 8192, 8192, EPI_RESID, false, true},
+      {13, 7168, 7168, EPI_RESID, true, true},   {8, 5120, 16384, EPI_RESID, true, true},
+      {8, 4096, 8192, EPI_RESID, true, true},    {16, 2048, 28672, EPI_RESID, true, false},
+      {8, 2048, 28672, EPI_RESID, true, true},   {16, 2048, 28672, EPI_RESID, false, true},
+      {16, 4096, 14336, EPI_RESID, true, true},  {24, 2048, 8192, EPI_RESID, true, true},
+      {25, 2048, 8192, EPI_RESID, true, false},  {32, 2048, 8192, EPI_RESID, false, true},
+      {24, 2048, 12288, EPI_RESID, true, false}, {32, 1024, 16384, EPI_RESID, false, false},
+      {24, 1024, 16384, EPI_RESID, false, true}, {32, 3072, 8192, EPI_RESID, true, true},
+      {32, 4096, 4096, EPI_RESID, true, true},   {33, 4096, 4096, EPI_RESID, true, false},
+      {32, 14336, 4096, EPI_SILU, false, true},  {13, 14336, 4096, EPI_SILU, true, false},
+  };
+  for (const Case &c : cases) CHECK(gemm_use_skinny(c.M, c.N, c.K, c.epi, c.tiled) == c.skinny);
+}
+
 // A workspace sized for a batch serves the smaller ones: attention's records
 // never shrink as the batch grows, and neither do the needs of a layer all of
 // attention (no split-K) and of one whose SiLU-gated GEMM splits K up to 64
@@ -346,6 +368,7 @@ int main(int argc, char **argv) {
   check_allocator();
   check_bad_configs();
   check_stream_tiles();
+  check_skinny_rule();
   check_random_shapes();
   check_workspace_growth();
   for (Work &w : read_works(argv[1])) {
