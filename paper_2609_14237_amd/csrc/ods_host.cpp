@@ -182,18 +182,6 @@ bool gemm_norm_skinny(int M, int N, int K, int epi, bool b_tiled) {
   return epi == EPI_SILU || gemm_use_skinny(M, N, K, epi, b_tiled);
 }
 
-// Dense GEMMs past 32 rows whose K is a whole number of 64-wide steps (fewer
-// rows: the whole-K kernel). The register-staged kernels lose at every size
-// measured, row-major weights: the narrow layer (hidden 2048, SwiGLU 8192) at
-// 100 rows qkv 16.1 -> 10.8 us, o_proj 15.9 -> 10.9, gate_up + SiLU 25.5 -> 20.0,
-// down 25.2 -> 15.9; the 8B-shaped layer at 100 rows 24.6 -> 16.7, 20.0 -> 16.3,
-// 69.7 -> 50.9 and 38.8 -> 35.9 us, its gate_up + SiLU at 33 to 64 rows
-// 48.0-50.4 -> 43.8-48.3 us. N <= 128 (the router) has too few 128-column tiles.
-bool gemm_use_stream(int M, int N, int K, int epi) {
-  if (N <= 128 || K % 64 != 0) return false;
-  return M > 32;
-}
-
 namespace {
 
 // Split K (1, 2, 4 or 8 ways, at least 8 steps per split) while the blocks
@@ -209,7 +197,57 @@ int stream_splits(int tiles, int steps) {
 
 int stream_n_tiles(int N, int epi) { return epi == EPI_SILU ? (N + 63) / 64 : (N + 127) / 128; }
 
+// Split-K of the decode tiles (up to 64 rows, and narrow outputs at any).
+// Too few tiles leaves HBM idle: split K up to 4 ways (8 for long K) until
+// there are about two blocks per compute unit, keeping at least 8 K steps
+// per block. The SiLU-gated GEMM is wide enough at decode batches and skips
+// the extra pass. A narrow output has few tiles at any batch: split it up to
+// 16 ways, down to 2 K steps per block.
+int decode_tiles(int M, int N, int K, int epi) {
+  const int bn = tile_n(N, K, epi);
+  return ((M + kDecodeBM - 1) / kDecodeBM) * ((N + bn - 1) / bn);
+}
+int decode_splits(int M, int N, int K, int epi) {
+  const int tiles = decode_tiles(M, N, K, epi), steps = (K + kDecodeBK - 1) / kDecodeBK;
+  const int want = epi == EPI_SILU ? 256 : 512;
+  const bool narrow = N <= 128;
+  const int max_s = narrow ? 16 : long_k(N, K, epi) ? 8 : 4, min_steps = narrow ? 2 : 8;
+  int s = 1;
+  while (tiles * s < want && s < max_s && steps / (s * 2) >= min_steps) s *= 2;
+  return s;
+}
+
 }  // namespace
+
+// Dense GEMMs past 32 rows whose K is a whole number of 64-wide steps (fewer
+// rows: the whole-K kernel). The register-staged kernels lose, row-major
+// weights: the narrow layer (hidden 2048, SwiGLU 8192) at 100 rows qkv 16.1 ->
+// 10.8 us, o_proj 15.9 -> 10.9, gate_up + SiLU 25.5 -> 20.0, down 25.2 -> 15.9;
+// the 8B-shaped layer at 100 rows 24.6 -> 16.7, 20.0 -> 16.3, 69.7 -> 50.9 and
+// 38.8 -> 35.9 us. N <= 128 (the router) has too few 128-column tiles.
+// The SiLU-gated GEMM of 33 to 64 rows goes by what it replaces, whatever the
+// row count (decode tile -> streaming at 33 and at 64 rows): here
+//  - unsplit from K 1024 on (N 14336, K 4096: 46.2 -> 41.0 and 47.7 -> 42.3 us;
+//    K 512 and N 8192 7.8 -> 8.4 and 8.1 -> 8.9);
+//  - split, where the decode tile has few blocks (K 4096, N 5504, 344 blocks:
+//    26.8 -> 25.9 and 29.1 -> 28.2; N 7168, 448 blocks: 28.2 -> 30.3 and 30.9 ->
+//    32.3) and the partials are small beside the weights: below K 2048 up to N =
+//    K^2 / 512 (K 1536, N 4096: 15.9 -> 13.9 and 16.4 -> 15.8; N 8192: 16.9 ->
+//    17.0 and 17.2 -> 19.4), below K 3072 but for N = 2 K, where the decode tile
+//    just fills the chip (K 2048, N 2816: 14.4 -> 13.1 and 15.5 -> 15.0, N 4096:
+//    15.5 -> 16.2 and 16.6 -> 18.6, N 8192: 21.8 -> 18.7 and 22.4 -> 21.2), and
+//    no 4-way split or more of a K much past N (K 5120, N 2816: 20.1 -> 20.1 and
+//    22.2 -> 23.5; K 4096, N 4096: 24.6 -> 18.9 and 25.7 -> 20.2).
+bool gemm_use_stream(int M, int N, int K, int epi) {
+  if (M <= 32 || N <= 128 || K % 64 != 0) return false;
+  if (M > 64 || epi != EPI_SILU) return true;
+  const int splits = stream_splits(stream_n_tiles(N, epi), K / 64);
+  if (splits == 1) return K >= 1024;
+  if (decode_tiles(M, N, K, epi) * decode_splits(M, N, K, epi) > 360) return false;
+  if (K < 2048) return (int64_t)N * 512 <= (int64_t)K * K;
+  if (splits >= 4 && K >= 4096 && N >= 2048 && 2 * K > 3 * N) return false;
+  return K >= 3072 || N != 2 * K;
+}
 
 // Past 64 rows a dense GEMM takes the 256-row tile unless that grid, split-K
 // included, would occupy fewer than half of the 256 compute units (small
@@ -269,20 +307,7 @@ int gemm_splits(int M, int N, int K, int epi, bool b_tiled) {
     while (tiles * s < 192 && s < 8 && steps / (s * 2) >= 8) s *= 2;
     return s;
   }
-  const int bn = tile_n(N, K, epi);
-  const int tiles = ((M + kDecodeBM - 1) / kDecodeBM) * ((N + bn - 1) / bn);
-  const int steps = (K + kDecodeBK - 1) / kDecodeBK;
-  int s = 1;
-  // Too few tiles leaves HBM idle: split K up to 4 ways (8 for long K) until
-  // there are about two blocks per compute unit, keeping at least 8 K steps
-  // per block. The SiLU-gated GEMM is wide enough at decode batches and skips
-  // the extra pass. A narrow output has few tiles at any batch: split it up to
-  // 16 ways, down to 2 K steps per block.
-  const int want = epi == EPI_SILU ? 256 : 512;
-  const bool narrow = N <= 128;
-  const int max_s = narrow ? 16 : long_k(N, K, epi) ? 8 : 4, min_steps = narrow ? 2 : 8;
-  while (tiles * s < want && s < max_s && steps / (s * 2) >= min_steps) s *= 2;
-  return s;
+  return decode_splits(M, N, K, epi);
 }
 
 size_t gemm_partial_bytes(int M, int N, int K, int epi, bool b_tiled) {

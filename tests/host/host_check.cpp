@@ -325,6 +325,24 @@ static void check_skinny_rule() {
   for (const Case &c : cases) CHECK(gemm_use_skinny(c.M, c.N, c.K, c.epi, c.tiled) == c.skinny);
 }
 
+// The SiLU-gated GEMM of 33 to 64 rows on row-major weights: decode tile or
+// streaming kernel, at shapes both were measured on.
+static void check_silu_rule() {
+  struct Case {
+    int N, K;
+    bool stream;
+  };
+  const Case cases[] = {{1024, 512, false},  {8192, 512, false},   {1024, 1024, true},   {4096, 1024, false},
+                        {8192, 1024, false}, {10240, 1024, true},  {4096, 1536, true},   {8192, 1536, false},
+                        {2816, 2048, true},  {4096, 2048, false},  {7168, 2048, false},  {8192, 2048, true},
+                        {4096, 3072, true},  {8192, 3072, true},   {4096, 4096, true},   {7168, 4096, false},
+                        {14336, 4096, true}, {5504, 4096, true},   {2048, 4096, false},  {2816, 5120, false},  {13824, 5120, true},  {28672, 8192, true},  {688, 256, false}};
+  for (int M : {33, 48, 64})
+    for (const Case &c : cases) CHECK(gemm_use_stream(M, c.N, c.K, EPI_SILU) == c.stream);
+  CHECK(gemm_use_stream(65, 4096, 1024, EPI_SILU) && gemm_use_stream(33, 4096, 1024, EPI_RESID));
+  CHECK(!gemm_use_stream(32, 14336, 4096, EPI_SILU) && !gemm_use_stream(100, 14336, 4104, EPI_SILU));
+}
+
 // A workspace sized for a batch serves the smaller ones: attention's records
 // never shrink as the batch grows, and neither do the needs of a layer all of
 // attention (no split-K) and of one whose SiLU-gated GEMM splits K up to 64
@@ -369,6 +387,7 @@ int main(int argc, char **argv) {
   check_bad_configs();
   check_stream_tiles();
   check_skinny_rule();
+  check_silu_rule();
   check_random_shapes();
   check_workspace_growth();
   for (Work &w : read_works(argv[1])) {
