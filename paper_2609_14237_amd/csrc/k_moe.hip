@@ -247,54 +247,62 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const uint16_t *__rest
 }
 
 // resid[b] = bf16(resid[b] + sum_j w[b, j] * yp[slot_pos[b*k + j]]), fp32
-// accumulation in slot order. One 16-byte vector per thread, a row over several
-// blocks. Bound by bytes at large batches and by the chain slot -> row -> add at
-// small ones: the slots and weights of eight experts load together, then their
-// rows (slots past the rows contribute nothing, as rows that were never read).
-// Top-8, 4096 wide: 10.0 -> 8.4 us at 512 tokens (40 MB), 8.2 -> 5.2 us at 24.
+// accumulation in slot order. One 16-byte vector per thread and trip. Bound by
+// the chain slot -> row -> add at small batches and by bytes at large ones: the
+// slots and weights of J experts load together, then their rows (slots past the
+// rows contribute nothing, as rows that were never read). J is the least of 1,
+// 2, 4 and 8 that covers k (loads past k repeat the last slot: with 8 of them
+// top-1 at 2048 tokens, 4096 wide, took 8.4 us, 6.0 with one), and a row goes
+// over several blocks (top-8, 4096 wide: 5.1 -> 2.8 us at 16 tokens, 9.0 -> 6.2
+// at 512). Once many wide rows are in flight (32 MB of yp), J = 1 and a block per
+// row, which keep fewer rows of yp open at a time, are faster (2048 tokens, 4096
+// wide: top-8 28.0 -> 25.3 us, top-4 17.9 -> 16.7; top-6 of 1024 tokens, 2048
+// wide, 25 MB: 4.4 us against 5.0).
+template <int J, bool WHOLE_ROW>
 __global__ __launch_bounds__(256) void moe_combine_kernel(const uint16_t *__restrict__ yp,
                                                           const float *__restrict__ w,
                                                           const int32_t *__restrict__ slot_pos, int k, int H,
                                                           int n_rows, uint16_t *__restrict__ resid) {
-  constexpr int J = 8;
-  const int b = blockIdx.x, v = blockIdx.y * 256 + threadIdx.x;
-  if (v >= H / 8) return;
-  u32x4 *r = (u32x4 *)(resid + (int64_t)b * H) + v;
+  const int b = blockIdx.x;
   const int32_t *sp = slot_pos + (int64_t)b * k;
   const float *wb = w + (int64_t)b * k;
-  const u32x4 x = *r;
-  float acc[8];
+  for (int v = blockIdx.y * 256 + threadIdx.x; v < H / 8; v += 256) {
+    u32x4 *r = (u32x4 *)(resid + (int64_t)b * H) + v;
+    const u32x4 x = *r;
+    float acc[8];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.f;
-  for (int j0 = 0; j0 < k; j0 += J) {
-    int pos[J];
-    float wj[J];
-    u32x4 y[J];
+    for (int q = 0; q < 8; ++q) acc[q] = 0.f;
+    for (int j0 = 0; j0 < k; j0 += J) {
+      int pos[J];
+      float wj[J];
+      u32x4 y[J];
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int jj = min(j0 + j, k - 1);
-      pos[j] = sp[jj];
-      wj[j] = wb[jj];
-    }
+      for (int j = 0; j < J; ++j) {
+        const int jj = min(j0 + j, k - 1);
+        pos[j] = sp[jj];
+        wj[j] = wb[jj];
+      }
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      const int row = min(max(pos[j], 0), n_rows - 1);
-      y[j] = *((const u32x4 *)(yp + (int64_t)row * H) + v);
-    }
+      for (int j = 0; j < J; ++j) {
+        const int row = min(max(pos[j], 0), n_rows - 1);
+        y[j] = *((const u32x4 *)(yp + (int64_t)row * H) + v);
+      }
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-      if (j0 + j >= k || pos[j] < 0 || pos[j] >= n_rows) continue;
+      for (int j = 0; j < J; ++j) {
+        if (j0 + j >= k || pos[j] < 0 || pos[j] >= n_rows) continue;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        acc[2 * q] += wj[j] * bf_lo(y[j][q]);
-        acc[2 * q + 1] += wj[j] * bf_hi(y[j][q]);
+        for (int q = 0; q < 4; ++q) {
+          acc[2 * q] += wj[j] * bf_lo(y[j][q]);
+          acc[2 * q + 1] += wj[j] * bf_hi(y[j][q]);
+        }
       }
     }
-  }
-  u32x4 o;
+    u32x4 o;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) o[q] = pack2(bf_lo(x[q]) + acc[2 * q], bf_hi(x[q]) + acc[2 * q + 1]);
-  *r = o;
+    for (int q = 0; q < 4; ++q) o[q] = pack2(bf_lo(x[q]) + acc[2 * q], bf_hi(x[q]) + acc[2 * q + 1]);
+    *r = o;
+    if (!WHOLE_ROW) break;
+  }
 }
 
 }  // namespace
@@ -327,7 +335,13 @@ hipError_t launch_gather_rows(const uint16_t *src, const int32_t *perm, const in
 hipError_t launch_moe_combine(const uint16_t *yp, const float *w, const int32_t *slot_pos, int B, int k,
                               int H, uint16_t *resid, hipStream_t s) {
   if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(moe_combine_kernel, dim3(B, (H / 8 + 255) / 256), dim3(256), 0, s, yp, w, slot_pos, k, H, B * k, resid);
+  const bool many = B >= 1024 && k >= 3 && H >= 2048 && (int64_t)B * k * H >= (int64_t)16 << 20;
+  auto kern = many     ? moe_combine_kernel<1, true>
+              : k == 1 ? moe_combine_kernel<1, false>
+              : k == 2 ? moe_combine_kernel<2, false>
+              : k <= 4 ? moe_combine_kernel<4, false>
+                       : moe_combine_kernel<8, false>;
+  hipLaunchKernelGGL(kern, dim3(B, many ? 1 : (H / 8 + 255) / 256), dim3(256), 0, s, yp, w, slot_pos, k, H, B * k, resid);
   return hipGetLastError();
 }
 
