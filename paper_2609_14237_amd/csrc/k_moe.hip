@@ -12,7 +12,8 @@ namespace ods {
 
 namespace {
 
-// Up to 64 experts, one per lane: each lane counts the lanes that go before it
+// Up to 64 experts (but top-1 on finished logits), one per lane: each lane
+// counts the lanes that go before it
 // (a larger logit, or an equal one of a lower id), so the ranks of all experts
 // come out of 64 lane broadcasts whatever k is, and one lane permutation puts
 // expert of rank r in lane r. Bound by latency: the split-K partials load in one
@@ -70,9 +71,9 @@ __global__ __launch_bounds__(256) void topk64_kernel(const float *__restrict__ l
   }
 }
 
-// One wave per token, more than 64 experts: top-k of the fp32 logits (ties ->
-// lower expert id), and softmax over the chosen k. E <= 256 (four logits per lane), k <= 64. With
-// splits > 1 the token's logits are the sum of the router's split-K partials,
+// One wave per token, more than 64 experts or top-1: top-k of the fp32 logits
+// (ties -> lower expert id), and softmax over the chosen k. E <= 256 (four
+// logits per lane), k <= 64. With splits > 1 the token's logits are the sum of the router's split-K partials,
 // added in split order as the reduce would, and are written to logits_out.
 __global__ __launch_bounds__(256) void topk_kernel(const float *__restrict__ logits, int B, int E, int k,
                                                    int32_t *__restrict__ ids, float *__restrict__ w,
@@ -311,7 +312,10 @@ hipError_t launch_topk(const float *logits, int B, int E, int k, int32_t *ids, f
                        const float *partial, int splits, float *logits_out) {
   if (B <= 0) return hipSuccess;
   if (splits > 1 && (!partial || !logits_out)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(E <= kWave ? topk64_kernel : topk_kernel, dim3((B + 3) / 4), dim3(256), 0, s, logits, B, E, k, ids,
+  // Top-1 on finished logits is one round of the general kernel: 2.6 us at 2048
+  // tokens of 64 experts, 3.2 by ranks (with 16 split-K partials 10.1 and 9.6).
+  const bool ranks = E <= kWave && (k > 1 || splits > 1);
+  hipLaunchKernelGGL(ranks ? topk64_kernel : topk_kernel, dim3((B + 3) / 4), dim3(256), 0, s, logits, B, E, k, ids,
                      w, partial, splits > 1 ? splits : 1, logits_out);
   return hipGetLastError();
 }

@@ -51,3 +51,24 @@ def test_topk_special_logits(E, k):
             p = np.exp(zz - zz[0])
             p = p / p.sum()
         np.testing.assert_allclose(wts[b], p, rtol=1e-5, atol=1e-6, equal_nan=True, err_msg=str(b))
+
+
+@pytest.mark.parametrize("E,k", [(64, 1), (64, 2), (48, 1), (100, 1)])
+def test_topk_joined_to_the_router_equals_the_cut(E, k):
+    """Router and top-k in one call (split-K partials summed by the top-k kernel) and as two calls: the same logits and
+    ids, weights to fp32 exp rounding. Top-1 of up to 64 experts takes another kernel in either form."""
+    say("top-k joined to the router", E, k)
+    cfg = W.LayerCfg(hidden=2048, n_q=2, n_kv=1, head_dim=64, n_experts=E, top_k=k, moe_ffn=64)
+    n = 40
+    s = Setup(W.Workload("topk_join", (cfg,), batch=n, ctx_lo=1, ctx_hi=4), seed=E + k)
+    s.reset_resid()
+    s.run(6, 7)
+    got = []
+    for cuts in ([7, 9], [7, 8, 9]):
+        for a, b in zip(cuts[:-1], cuts[1:]):
+            s.run(a, b)
+        torch.cuda.synchronize()
+        got.append([s.buf(x, n, m).clone() for x, m in (("logits", E), ("topk_ids", k), ("topk_w", k))])
+    (z0, i0, w0), (z1, i1, w1) = got
+    assert torch.equal(z0, z1) and torch.equal(i0, i1)
+    assert (w0 - w1).abs().max() <= 1e-6
