@@ -136,7 +136,8 @@ typedef struct {
  * [0, pool_pages) are skipped by the kernels. attn_core numbers the (sequence,
  * KV head, window page) units of the batch and gives every wave of its grid an
  * equal contiguous range of them; split_pages fixes the range length in pages
- * (0: library choice, the batch's pages over all waves, at least 8 each).
+ * (0: library choice, the batch's pages over all waves, at least 4 each, or 2
+ * with 64-wide heads).
  * attn_core takes batch <= 4096 and batch * n_kv * window pages < 2^30
  * (ODS_EUNSUPPORTED otherwise).
  *

@@ -6,7 +6,7 @@
 // Work split: the (sequence b, KV head g, page of b's attended window) units
 // of the whole batch are numbered b-major, and wave r of the grid takes the
 // contiguous unit range [r*S, (r+1)*S) with S = ceil(total / waves) (at least
-// attn_min_pages), so every wave streams the same number of KV bytes however ragged
+// attn_min_pages; wide groups may take longer ranges), so every wave streams the same number of KV bytes however ragged
 // the contexts are. A range may end inside a sequence or cover several short
 // ones; each (b, g) piece is a segment. A sequence that one segment covers is
 // written to o directly; otherwise every segment leaves a partial record
@@ -141,9 +141,20 @@ __global__ __launch_bounds__(64 * attn_waves(D)) __attribute__((amdgpu_waves_per
   constexpr int LPP = 2 * (kPage * D * 2 / 1024);  // 16-byte direct-to-LDS loads per page and lane
   uint8_t *const slots = (uint8_t *)smem_i + (((2 * B + 1) * 4 + 15) & ~15) + wave * kSlots * SLOT;
   const int total = __builtin_amdgcn_readfirstlane(s_pre[B]);
+  // Wide groups leave heavy records (16 rows of a 64-wide head: written and read
+  // again, two pages' bytes), so short ranges cost them more: with 64-wide heads
+  // half the waves share the units while ranges are below 16 pages and each
+  // wave has one (group 16, 256 sequences of 256 tokens 17.3 -> 14.1 us, 1500
+  // of them 38.2 -> 34.4); 128-wide heads round ranges of 7 pages up to 8 (group
+  // 8, 100 sequences of 256 tokens, 4 KV heads: 20.9 -> 19.7 us).
+  int S = seg_pages;
+  if (seg_pages <= 0) {
+    if (D == 64 && group > 8 && 2 * total > 3 * n_waves && total < 16 * n_waves) n_waves /= 2;
+    S = max(attn_min_pages(D), (total + n_waves - 1) / n_waves);
+    if (D == 128 && group >= 8 && S == 7) S = 8;
+  }
   // Split over fewer waves than the grid has, the working ones spread over all workgroups.
   const int r0 = n_waves < (int)gridDim.x * WAVES ? wave * (int)gridDim.x + (int)blockIdx.x : blockIdx.x * WAVES + wave;
-  const int S = seg_pages > 0 ? seg_pages : max(attn_min_pages(D), (total + n_waves - 1) / n_waves);
   const int64_t page_stride = 2 * (int64_t)n_kv * BLK;
   const int64_t v_off = (int64_t)n_kv * BLK;
 

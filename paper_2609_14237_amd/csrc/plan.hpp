@@ -86,7 +86,7 @@ int64_t tiled_weight_elems(int out, int in, bool gated, int groups);
 // compute unit, and a log-sum-exp merge of sequences that span several waves.
 constexpr int kMaxAttnBatch = 4096;  // the kernel keeps per-sequence contexts and a prefix in LDS
 struct AttnPlan {
-  int seg_pages;    // pages per wave range; 0: total / waves (at least 8)
+  int seg_pages;    // pages per wave range; 0: total / waves (at least attn_min_pages)
   int grid;         // workgroups of the attention kernel
   int waves;        // waves the units are split over (at most grid * attn_waves)
   int64_t records;  // partial-record slots per query-head group
