@@ -80,11 +80,12 @@ size_t layer_ws_bytes(const ods_layer &L, const ods_batch *b, int cus) {
   const int B = b->batch;
   const bool t = tiled(L);
   size_t w = align_up(attn_ws_bytes(B, c.n_q, c.n_kv, c.head_dim, plan_for(c, b, cus)));
-  // A batch of 65 to 128 rows also covers 64, whose split-K may be the larger
-  // one (a SiLU-gated GEMM that runs unsplit past 64 rows).
+  // A batch of 65 to 128 rows also covers 64 and 80, whose split-K may be the
+  // larger one (a SiLU-gated GEMM that runs unsplit past them).
   auto g = [&](int N, int K, int epi, bool bt) {
     w = std::max(w, align_up(gemm_partial_bytes(B, N, K, epi, bt)));
-    if (B > 64 && B <= 128) w = std::max(w, align_up(gemm_partial_bytes(64, N, K, epi, bt)));
+    if (B > 64 && B <= 128)
+      for (const int b : {64, std::min(B, 80)}) w = std::max(w, align_up(gemm_partial_bytes(b, N, K, epi, bt)));
   };
   g(qkv_dim(c), c.hidden, EPI_BF16, t);
   g(c.hidden, c.n_q * c.head_dim, EPI_RESID, t);
@@ -271,17 +272,18 @@ bool gemm_use_stream(int M, int N, int K, int epi) {
 //    48.6 us; N 10240 and K 8192 30.1 against 37.9 us);
 //  - a split grid that they fill without split-K over a short K (gate_up + SiLU
 //    of the narrow layer, N 8192 and K 2048, at 100 rows 22.1 -> 19.7 us,
-//    partials and reduce gone; N 6144 19.4 -> 18.4). At K 2560 the two are level
-//    (N 6144 at 65 to 128 rows 20.2-24.7 and 21.3-23.4 us), at K 3584
-//    they lose (N 6144 at 65 rows 24.4 against 28.4 us, at 128 rows 29.1
-//    against 30.3 us).
+//    partials and reduce gone; N 6144 19.4 -> 18.4; with 172 blocks at N 5504
+//    they gain past 80 rows, at 65 17.4 -> 18.3 us, at 128 20.7 -> 19.4). At K
+//    2560 the two are level (N 6144 at 65 to 128 rows 20.2-24.7 and 21.3-23.4
+//    us), at K 3584 they lose (N 6144 at 65 rows 24.4 against 28.4 us, at 128
+//    rows 29.1 against 30.3 us).
 int gemm_stream_rows(int M, int N, int K, int epi) {
   if (M <= 64) return 64;
   const int tiles = (M + 255) / 256 * stream_n_tiles(N, epi);
   const int s = N % 4 != 0 ? 1 : stream_splits(tiles, K / 64);
   if (M <= 128 && s > 1) {
     const int blocks64 = 2 * tiles * stream_splits(2 * tiles, K / 64);
-    if ((tiles * s < 192 && blocks64 > tiles * s) || (K <= 2048 && 2 * tiles >= 192)) return 64;
+    if ((tiles * s < 192 && blocks64 > tiles * s) || (K <= 2048 && 2 * tiles >= (M > 80 ? 160 : 192))) return 64;
   }
   return tiles * s < 128 ? 64 : 256;
 }

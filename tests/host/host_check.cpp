@@ -242,7 +242,8 @@ static void check_stream_tiles() {
       {100, 8192, 2048, EPI_SILU, 64, 1},   {100, 6144, 2048, EPI_SILU, 64, 1},
       {65, 5120, 13824, EPI_RESID, 256, 4}, {128, 5120, 5120, EPI_RESID, 256, 4},
       {100, 10240, 8192, EPI_BF16, 256, 2}, {128, 9216, 7168, EPI_BF16, 256, 2},
-      {65, 5120, 3072, EPI_BF16, 256, 4},   {128, 5504, 2048, EPI_SILU, 256, 2},
+      {65, 5120, 3072, EPI_BF16, 256, 4},   {65, 5504, 2048, EPI_SILU, 256, 2},
+      {81, 5504, 2048, EPI_SILU, 64, 1},    {80, 6144, 2048, EPI_SILU, 64, 1},
       {100, 8192, 4096, EPI_SILU, 256, 2},
   };
   for (const Case &c : cases) {
@@ -346,7 +347,7 @@ static void check_silu_rule() {
 // A workspace sized for a batch serves the smaller ones: attention's records
 // never shrink as the batch grows, and neither do the needs of a layer all of
 // attention (no split-K) and of one whose SiLU-gated GEMM splits K up to 64
-// rows and runs unsplit at 65 to 128.
+// rows (N 5504: 80) and runs unsplit up to 128.
 static void check_workspace_growth() {
   for (int D : {64, 128})
     for (int n_kv : {1, 2, 8})
@@ -375,6 +376,8 @@ static void check_workspace_growth() {
     L.weight_layout = tiled ? ODS_WEIGHTS_TILED : ODS_WEIGHTS_ROWS;
     L.cfg = ods_layer_cfg{2048, 32, 8, 64, 8192, 0, 0, 0, 0, 10000.f, 1e-6f};
     for (int B = 33; B < 128; ++B) CHECK(need(B) <= need(B + 1));
+    L.cfg.ffn = 5504;
+    for (int B = 65; B < 128; ++B) CHECK(need(B) <= need(B + 1));
   }
 }
 
