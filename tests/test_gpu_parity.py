@@ -415,13 +415,15 @@ def test_dense_8b_shape_small_batch():
 # ---------------------------------------------------------------- GEMM tile paths
 
 @pytest.mark.parametrize("batch", [65, 100, 128, 200, 300])
-def test_layer_across_gemm_tile_paths(batch):
-    """Batches above 64 rows take the 512-thread large-M GEMM tiles up to 128
-    rows; past 128 the streaming kernel runs every GEMM whose K is a multiple
-    of 64, on 64-row tiles at these narrow widths, and down (K = 688) stays on
-    the 256-row large-M tile. F = 688 leaves K and SiLU-N tails, H = 640 an N
+@pytest.mark.parametrize("hidden", [640, 648])
+def test_layer_across_gemm_tile_paths(hidden, batch):
+    """Past 64 rows the streaming kernel runs every GEMM whose K is a multiple
+    of 64 (hidden 640: all but down, on 64-row tiles at these narrow widths),
+    and the 512-thread large-M tiles of 128 rows, past 128 rows 256, the rest:
+    down (K = 688), and with hidden 648 qkv, the SiLU-gated and the unfused
+    gate_up as well. F = 688 leaves K and SiLU-N tails, either hidden an N
     tail of the 128-column tile."""
-    cfg = W.LayerCfg(hidden=640, n_q=10, n_kv=2, head_dim=64, ffn=688)
+    cfg = W.LayerCfg(hidden=hidden, n_q=10, n_kv=2, head_dim=64, ffn=688)
     w = W.Workload("gemm_paths", (cfg,), batch=batch, ctx_lo=1, ctx_hi=70)
     say("gemm tile paths, batch", batch)
     s = Setup(w, seed=12)

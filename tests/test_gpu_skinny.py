@@ -95,16 +95,23 @@ def test_router_against_float64(hidden, experts, batch):
 
 
 @pytest.mark.parametrize("batch", [1, 8, 9, 16])
-@pytest.mark.parametrize("hidden,ffn", [(2056, 64), (520, 16), (4104, 128)])
-def test_norm_joins_gate_up(hidden, ffn, batch):
+@pytest.mark.parametrize("hidden,ffn,tiled", [
+    (2056, 64, False), (520, 16, False), (4104, 128, False),
+    # one gate and one up fragment per block, two and two (past 4096 columns), four and four (past 8192)
+    (704, 1088, False), (704, 1088, True), (1000, 4232, False), (1024, 4224, True), (1000, 8264, False),
+    (1024, 8320, True), (7680, 8320, False), (7680, 8320, True)])
+def test_norm_joins_gate_up(hidden, ffn, tiled, batch):
     """ffn_norm, gate_up and SiLU in one call: hn is the norm of the residual to one bf16 rounding (2^-8), act the gated
     products of the float64 normalised rows. Bound: each factor of a product is rounded to bf16 once (2^-9, here the row
     before or after its 1 / rms), so a sum is off by at most 2^-8 of sum |hn||w| with the fp32 order; SiLU(gate) * up
     carries both through (sensitivities at most 1.1 |up| and |silu|) and is rounded once. Few blocks against rows whose
-    last 64-wide slice is short: every thread writes several slices of hn, with short ones among them."""
-    print(f"[case] norm + gate_up + SiLU hidden {hidden} ffn {ffn} batch {batch}", file=sys.stderr, flush=True)
+    last 64-wide slice is short: every thread writes several slices of hn, with short ones among them. Wide outputs on
+    tiled weights run this launch only with their norm; hidden 7680 is the widest gain it holds, at 16 rows and four
+    fragments the most LDS it asks for."""
+    print(f"[case] norm + gate_up + SiLU hidden {hidden} ffn {ffn} {'tiled' if tiled else 'rows'} batch {batch}",
+          file=sys.stderr, flush=True)
     cfg = W.LayerCfg(hidden=hidden, n_q=2, n_kv=1, head_dim=64, ffn=ffn)
-    s = Setup(W.Workload("skinny_norm", (cfg,), batch=batch, ctx_lo=1, ctx_hi=20), seed=batch + hidden)
+    s = Setup(W.Workload("skinny_norm", (cfg,), batch=batch, ctx_lo=1, ctx_hi=20), seed=batch + hidden, tiled=tiled)
     s.reset_resid()
     s.run(6, 9)
     torch.cuda.synchronize()
