@@ -113,20 +113,38 @@ static void check_block_ranges(const Work &w, int cus) {
       CHECK(range_ws_bytes(&blk, a, b, &batch, cus) <= ws);
       ods_state st = fake_state(ws);
       CHECK(validate_range(&blk, a, b, &batch, &st, cus) == ODS_OK);
-      int covered = 0;
+      int covered = 0, appended = -1;  // operator whose launch last appended the KV
       for (int i = 0; i < b - a;) {
         Launch L;
         plan_launch(&blk, a, b, i, &batch, &st, cus, &L);
         CHECK(L.n_ops >= 1 && L.n_ops <= 3 && i + L.n_ops <= b - a);
         CHECK(L.layer == op_at(&blk, a + i).layer && L.what != nullptr);
-        if (L.kind == LK_GEMM || L.kind == LK_QKV_ROPE) {
+        const OpKind kind = op_at(&blk, a + i).kind;
+        if (L.kind == LK_GEMM || L.kind == LK_GEMM_NORM || L.kind == LK_SKINNY || L.kind == LK_QKV_ROPE ||
+            L.kind == LK_ROUTER_TOPK) {
           const GemmArgs &g = L.gemm;
           CHECK(g.M == w.batch || g.group_off != nullptr);
           CHECK(g.splits == 1 || g.splits == 2 || g.splits == 4 || g.splits == 8 || g.splits == 16);
           if (g.splits > 1)
             CHECK((size_t)g.splits * g.M * g.N * (g.epi == EPI_SILU ? 2 : 1) * sizeof(float) <= ws);
           CHECK(g.N > 0 && g.K > 0);
+          if (g.b_tiled) CHECK(g.K % 64 == 0);
         }
+        if (L.kind == LK_GEMM_NORM) {  // split-K residual GEMM, the norm of its rows behind it
+          CHECK(kind == K_O_PROJ || kind == K_DOWN);
+          CHECK(L.gemm.splits > 1 && L.gemm.defer_reduce && L.gemm.epi == EPI_RESID);
+          CHECK(L.gemm.N <= kReduceNormMaxN && L.gain && L.out && L.n_ops == 2);
+        }
+        if (L.kind == LK_SKINNY) {  // whole-K GEMM with its norm, its RoPE or both
+          CHECK(kind == K_ATTN_NORM || kind == K_FFN_NORM || kind == K_QKV);
+          CHECK(L.gemm.splits == 1 && L.gemm.M <= kSkinnyRows && (L.gain != nullptr || L.has_rope));
+          CHECK(!L.gain || (L.gemm.M <= 16 && L.gemm.K <= kSkinnyNormMaxK && L.out));
+          CHECK(L.has_rope ? L.gemm.epi == EPI_BF16 : L.gemm.epi == EPI_SILU);
+          CHECK(L.n_ops == (L.gain ? 3 : 2));
+          if (L.has_rope && L.rope.do_append) appended = a + i + L.n_ops;
+        }
+        if (L.kind == LK_NONE) CHECK(kind == K_KV_APPEND && a + i == appended);
+        if (kind == K_KV_APPEND && a + i == appended) CHECK(L.kind == LK_NONE);
         if (L.kind == LK_ATTENTION) {
           CHECK(L.attn.plan.grid >= 1 && L.attn.plan.grid <= (cus > 0 ? cus : 1));
           CHECK(attn_ws_bytes(w.batch, L.attn.n_q, L.attn.n_kv, L.attn.D, L.attn.plan) <= ws);
@@ -399,6 +417,11 @@ int main(int argc, char **argv) {
       const ods_block blk{(int32_t)w.layers.size(), w.layers.data()};
       if (check_block(&blk) != ODS_OK) continue;  // a shape the tiled layout does not take
       for (int cus : {1, 80, 256, 304}) check_block_ranges(w, cus);
+      Work small = w;  // either side of the whole-K kernel's row limits
+      for (int B : {1, 16, 17, 32, 33}) {
+        small.batch = B;
+        check_block_ranges(small, 256);
+      }
     }
   }
   printf("host_check OK (%d checks)\n", g_checks);
