@@ -6,7 +6,8 @@
 // steps run elsewhere: up to 32 rows in the whole-K kernel (k_gemm_skinny.hip),
 // past that in the direct-to-LDS streaming kernel (k_gemm_stream.hip). Here are
 // the rest: K that is not a multiple of 64, outputs of at most 128 columns
-// (the router), and the split-K reduce.
+// (the router), row-major weights those two lose on (long K at 17 to 32 rows,
+// some SiLU-gated GEMMs of 33 to 64), and the split-K reduce.
 //
 // Tiling: 256 threads = 4 waves; block tile BM x BN outputs, K step BK; LDS
 // double buffering (global loads of step k+1 are in flight while step k runs

@@ -5,7 +5,7 @@
 // Bound by the weight stream. At these batches the tiled kernels lose to their
 // own fixed parts: 64 activation rows staged whatever M is, split-K partials
 // written and summed by a second launch, and few K steps per block. Here a
-// block owns 16 or 32 output columns for the whole of K, its waves take every
+// block owns 16 to 64 output columns for the whole of K, its waves take every
 // W-th 64-wide K step each and meet once, in LDS, at the end: no partials, no
 // reduce launch, and no barrier in the loop. Each wave streams its steps (its
 // rows of B, and only the 8-row groups of A that exist) through an LDS ring of

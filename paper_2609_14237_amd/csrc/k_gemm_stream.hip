@@ -1,7 +1,8 @@
-// Weight-streaming bf16 MFMA GEMM for dense products past 32 rows, for the
-// grouped expert GEMMs (any rows per group), and for wide outputs on tiled
-// weights at any batch (B stored as the LDS image of each K step's tile, read
-// as one contiguous run per block): C[m, n] = sum_k A[m, k] * B[n, k] with the same epilogues as the
+// Weight-streaming bf16 MFMA GEMM for dense products past 32 rows (but some
+// SiLU-gated ones of up to 64, gemm_use_stream), for the grouped expert GEMMs
+// (any rows per group), and for what the whole-K kernel leaves of up to 32 rows
+// on tiled weights (wide or large ones, gemm_use_skinny; B is stored as the LDS
+// image of each K step's tile, read as one contiguous run per block): C[m, n] = sum_k A[m, k] * B[n, k] with the same epilogues as the
 // other GEMM kernels. Built on its own with MFMA results in
 // VGPRs (build.py passes -amdgpu-mfma-vgpr-form for this file only), which
 // keeps the accumulators in place across the K loop.

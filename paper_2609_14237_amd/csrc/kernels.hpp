@@ -18,7 +18,8 @@ int num_cus();
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
 // Sum of split-K partials plus the epilogue (after a partial-writing launch).
 hipError_t launch_splitk_reduce(const GemmArgs &a, hipStream_t s);
-// Weight-streaming kernel (K % 64 == 0): dense GEMMs past 32 rows, grouped GEMMs, and wide outputs on tiled weights.
+// Weight-streaming kernel (K % 64 == 0): grouped GEMMs, and what gemm_use_stream takes of the dense ones (row-major) or
+// gemm_use_skinny leaves (tiled weights).
 hipError_t launch_gemm_stream(const GemmArgs &a, hipStream_t s);
 // Whole-K kernel for up to kSkinnyRows rows (dense GEMMs, both weight layouts, splits = 1).
 hipError_t launch_gemm_skinny(const GemmArgs &a, hipStream_t s);

@@ -65,7 +65,8 @@ bool gemm_norm_skinny(int M, int N, int K, int epi, bool b_tiled);
 bool use_big(int M, int N);            // 64 < M: the large-M tile
 bool long_k(int N, int K, int epi);    // narrow output with K >= 2N (the down projection)
 int tile_n(int N, int K, int epi);     // decode tile width
-// Weight-streaming kernel: dense GEMMs past 32 rows, grouped GEMMs, and on tiled weights what the whole-K kernel leaves.
+// Weight-streaming kernel on row-major weights, dense (grouped GEMMs, and tiled weights the whole-K kernel leaves, always
+// take it where K % 64 == 0).
 bool gemm_use_stream(int M, int N, int K, int epi);
 int gemm_stream_rows(int M, int N, int K, int epi);  // dense block rows: 64 or 256
 int gemm_stream_splits(int M, int N, int K, int epi);
